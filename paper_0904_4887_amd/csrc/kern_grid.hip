@@ -7,6 +7,7 @@
 //   (A u)_n = sum over the 6 neighbours m of n of
 //             1/2 (eps_n + eps_m) (u_m - u_n) / h_d^2.
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 
 #include "dwp_internal.h"
@@ -430,17 +431,15 @@ template <> __device__ __forceinline__ double cxv<double>(const LevelArgs &a, in
 // smoother only shapes the preconditioner, so the last bit of the quotient
 // does not matter; in FP64 two Newton steps bring the estimate to full
 // precision.
-__device__ __forceinline__ float gs_value(float off, float f, float diag) {
-    return (off - f) * __builtin_amdgcn_rcpf(diag);
-}
-__device__ __forceinline__ double gs_value(double off, double f, double diag) {
+__device__ __forceinline__ float gs_recip(float diag) { return __builtin_amdgcn_rcpf(diag); }
+__device__ __forceinline__ double gs_recip(double diag) {
     double r = __builtin_amdgcn_rcp(diag);
     double e = __builtin_fma(-diag, r, 1.0);
     r = __builtin_fma(r, e, r);
     e = __builtin_fma(-diag, r, 1.0);
-    r = __builtin_fma(r, e, r);
-    return (off - f) * r;
+    return __builtin_fma(r, e, r);
 }
+template <class T> __device__ __forceinline__ T gs_value(T off, T f, T diag) { return (off - f) * gs_recip(diag); }
 }  // namespace
 }  // namespace dwp
 #include "band_sweep.h"
@@ -1262,14 +1261,80 @@ __device__ void bt_prolong(const LevelDesc<T> &F, const LevelDesc<T> &C) {
     __syncthreads();
 }
 
-constexpr int BOTTOM_LDS = 2048;  // coarsest level staged in LDS when its ghosted size fits
+// `sweeps` sweeps of a level whose u lies in LDS, each thread holding its
+// points' six face weights, reciprocal diagonal and right-hand side in
+// registers (K points of each colour per thread): a colour then costs six LDS
+// reads and one write per point and a barrier, where bt_smooth reads thirteen
+// values and divides the index again.  Same operations on the same values in
+// the same order as bt_smooth.  Latency-bound (one workgroup): 64 sweeps of
+// 252 points in float32 with the levels above them took 90 us a cycle, now 53
+// (kernel trace).  For the one or two sweeps of the other bottom levels the
+// setup costs what it saves (18.9 against 21.1 us a V(1,1) cycle), so they
+// keep bt_smooth.
+template <int K, class T>
+__device__ void bt_sweeps_reg(const LevelDesc<T> &d, int sweeps) {
+    const int nx = d.a.nx, ny = d.a.ny, half = nx / 2;
+    const int per = half * ny * d.a.nw, plane = nx * ny;
+    const T cx = cxv<T>(d.a, 0), cy = cxv<T>(d.a, 1), cz = cxv<T>(d.a, 2);
+    T w[2][K][6], rd[2][K], fv[2][K];
+    int g[2][K], ox[2][K], oy[2][K];  // point; its x and y neighbours as two 16-bit indices each
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int m = 0; m < K; ++m) {
+            const int q = min((int)(threadIdx.x + m * blockDim.x), per - 1);
+            const int qh = bt_div(q, d.mh), t = q - qh * half;
+            const int kk = bt_div(qh, d.my), j = qh - kk * ny;
+            const int i = 2 * t + ((j + kk + c) & 1);
+            const int li = kk * plane + j * nx + i, gi = li + plane;
+            const int xp = gi - i + wrap_p(i, nx), xm = gi - i + wrap_m(i, nx);
+            const int yp = gi + (wrap_p(j, ny) - j) * nx, ym = gi + (wrap_m(j, ny) - j) * nx;
+            const T e0 = d.e[gi];
+            T *ww = w[c][m];
+            ww[0] = cx * (e0 + d.e[xp]); ww[1] = cx * (e0 + d.e[xm]);
+            ww[2] = cy * (e0 + d.e[yp]); ww[3] = cy * (e0 + d.e[ym]);
+            ww[4] = cz * (e0 + d.e[gi + plane]); ww[5] = cz * (e0 + d.e[gi - plane]);
+            rd[c][m] = gs_recip(T(0.5) * (ww[0] + ww[1] + ww[2] + ww[3] + ww[4] + ww[5]));
+            fv[c][m] = d.f[li];
+            g[c][m] = gi;
+            ox[c][m] = xp | (xm << 16);
+            oy[c][m] = yp | (ym << 16);
+        }
+    for (int s = 0; s < sweeps; ++s) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+#pragma unroll
+            for (int m = 0; m < K; ++m)
+                if ((int)(threadIdx.x + m * blockDim.x) < per) {
+                    const T *ww = w[c][m];
+                    const int gi = g[c][m], x2 = ox[c][m], y2 = oy[c][m];
+                    const T off = T(0.5) * (ww[0] * d.u[x2 & 0xFFFF] + ww[1] * d.u[x2 >> 16] +
+                                            ww[2] * d.u[y2 & 0xFFFF] + ww[3] * d.u[y2 >> 16] +
+                                            ww[4] * d.u[gi + plane] + ww[5] * d.u[gi - plane]);
+                    d.u[gi] = (off - fv[c][m]) * rd[c][m];
+                }
+            __syncthreads();
+        }
+    }
+}
+// Registers hold two points of each colour per thread in float64, three in
+// float32 (1024 threads leave 128 registers each; a fourth spills); larger
+// coarsest levels sweep through bt_smooth.
+template <class T>
+__device__ void bt_coarse(const LevelDesc<T> &d, int sweeps) {
+    const int per = d.a.nx / 2 * d.a.ny * d.a.nw, nt = (int)blockDim.x;
+    if (per <= nt) { bt_sweeps_reg<1>(d, sweeps); return; }
+    if (per <= 2 * nt) { bt_sweeps_reg<2>(d, sweeps); return; }
+    if constexpr (sizeof(T) == 4)
+        if (per <= 3 * nt) { bt_sweeps_reg<3>(d, sweeps); return; }
+    for (int k = 0; k < sweeps; ++k) { bt_smooth(d, 0); bt_smooth(d, 1); }
+}
 
 // V-cycle over levels L[0..nl-1] of the bottom set; L[0].f is given and
-// L[0].u holds the initial guess.  The coarsest level's sweeps run out of LDS
-// when it is small enough.
+// L[0].u holds the initial guess.  Out of global memory: for sets whose first
+// level's u and eps do not fit the LDS (thin levels with wide ghost planes).
 template <class T>
 __global__ void __launch_bounds__(1024) k_vcycle_bottom(Bottom<T> B) {
-    __shared__ T lu[BOTTOM_LDS], lf[BOTTOM_LDS], le[BOTTOM_LDS];
     for (int l = 0; l + 1 < B.nl; ++l) {
         for (int k = 0; k < B.pre; ++k) { bt_smooth(B.L[l], 0); bt_smooth(B.L[l], 1); }
         bt_residual(B.L[l]);
@@ -1277,22 +1342,7 @@ __global__ void __launch_bounds__(1024) k_vcycle_bottom(Bottom<T> B) {
     }
     {
         const LevelDesc<T> &c = B.L[B.nl - 1];
-        const int plane = c.a.nx * c.a.ny;
-        const int ng = plane * (c.a.nw + 2), ni = plane * c.a.nw;
-        if (ng <= BOTTOM_LDS) {
-            for (int q = threadIdx.x; q < ng; q += blockDim.x) { lu[q] = c.u[q]; le[q] = c.e[q]; }
-            for (int q = threadIdx.x; q < ni; q += blockDim.x) lf[q] = c.f[q];
-            __syncthreads();
-            LevelDesc<T> d = c;
-            d.u = lu;
-            d.f = lf;
-            d.e = le;
-            for (int k = 0; k < B.coarse; ++k) { bt_smooth(d, 0); bt_smooth(d, 1); }
-            for (int q = threadIdx.x; q < ng; q += blockDim.x) c.u[q] = lu[q];
-            __syncthreads();
-        } else {
-            for (int k = 0; k < B.coarse; ++k) { bt_smooth(c, 0); bt_smooth(c, 1); }
-        }
+        for (int k = 0; k < B.coarse; ++k) { bt_smooth(c, 0); bt_smooth(c, 1); }
     }
     for (int l = B.nl - 2; l >= 0; --l) {
         bt_prolong(B.L[l], B.L[l + 1]);
@@ -1300,15 +1350,21 @@ __global__ void __launch_bounds__(1024) k_vcycle_bottom(Bottom<T> B) {
     }
 }
 
-// The same V-cycle with every array of the bottom set in LDS (up to 160 KB
-// per workgroup on gfx950): the first level's u and f and every level's eps
-// are staged in once, u is written back at the end, and every phase between
-// reads and writes LDS only.  off[4 l + {0,1,2,3}] are the element offsets of
-// level l's u (ghosted), f, r (interior) and eps (ghosted) in LDS.
+// The same V-cycle out of LDS (up to 160 KB per workgroup on gfx950): the
+// first level's u and f and every level's eps are staged in once, u is written
+// back at the end, and every phase between reads and writes LDS -- all of it
+// (TOP 0), or all but the first level's residual (TOP 1), which is written and
+// read once a cycle, or but that residual and the first level's f (TOP 2),
+// which is read once per point update: the two largest arrays that a set too
+// large for the LDS can leave in memory at the least cost (16 x 16 x 19 over
+// 8 x 8 x 9 points in float64, 141 KB without the residual: 118 us a cycle out
+// of global memory, 51 us so).  off[4 l +
+// {0,1,2,3}] are the element offsets of level l's u (ghosted), f, r (interior)
+// and eps (ghosted) in LDS.
 struct BottomLds {
     int off[4 * MAX_BOTTOM];
 };
-template <class T>
+template <class T, int TOP>
 __global__ void __launch_bounds__(1024) k_vcycle_bottom_lds(Bottom<T> B, BottomLds O) {
     extern __shared__ __align__(16) unsigned char bl_raw[];
     T *lds = reinterpret_cast<T *>(bl_raw);
@@ -1318,6 +1374,14 @@ __global__ void __launch_bounds__(1024) k_vcycle_bottom_lds(Bottom<T> B, BottomL
         d.f = lds + O.off[4 * l + 1];
         d.r = lds + O.off[4 * l + 2];
         d.e = lds + O.off[4 * l + 3];
+        return d;
+    };
+    auto D0 = [&]() {
+        LevelDesc<T> d = B.L[0];
+        d.u = lds + O.off[0];
+        if constexpr (TOP < 2) d.f = lds + O.off[1];
+        if constexpr (TOP < 1) d.r = lds + O.off[2];
+        d.e = lds + O.off[3];
         return d;
     };
     for (int l = 0; l < B.nl; ++l) {
@@ -1331,23 +1395,27 @@ __global__ void __launch_bounds__(1024) k_vcycle_bottom_lds(Bottom<T> B, BottomL
         const int ni = a.nx * a.ny * a.nw, ng = ni + 2 * a.nx * a.ny;
         T *u = lds + O.off[0], *f = lds + O.off[1];
         for (int q = threadIdx.x; q < ng; q += blockDim.x) u[q] = B.L[0].u[q];
-        for (int q = threadIdx.x; q < ni; q += blockDim.x) f[q] = B.L[0].f[q];
+        if constexpr (TOP < 2)
+            for (int q = threadIdx.x; q < ni; q += blockDim.x) f[q] = B.L[0].f[q];
     }
     __syncthreads();
-    for (int l = 0; l + 1 < B.nl; ++l) {
-        const LevelDesc<T> d = D(l);
+    auto down = [&](const LevelDesc<T> &d, const LevelDesc<T> &c) {
         for (int k = 0; k < B.pre; ++k) { bt_smooth(d, 0); bt_smooth(d, 1); }
         bt_residual(d);
-        bt_restrict_zero(d, D(l + 1));
-    }
-    {
-        const LevelDesc<T> c = D(B.nl - 1);
-        for (int k = 0; k < B.coarse; ++k) { bt_smooth(c, 0); bt_smooth(c, 1); }
-    }
-    for (int l = B.nl - 2; l >= 0; --l) {
-        const LevelDesc<T> d = D(l);
-        bt_prolong(d, D(l + 1));
+        bt_restrict_zero(d, c);
+    };
+    auto up = [&](const LevelDesc<T> &d, const LevelDesc<T> &c) {
+        bt_prolong(d, c);
         for (int k = 0; k < B.post; ++k) { bt_smooth(d, 1); bt_smooth(d, 0); }
+    };
+    if (B.nl == 1) {
+        bt_coarse(D0(), B.coarse);
+    } else {
+        down(D0(), D(1));
+        for (int l = 1; l + 1 < B.nl; ++l) down(D(l), D(l + 1));
+        bt_coarse(D(B.nl - 1), B.coarse);
+        for (int l = B.nl - 2; l >= 1; --l) up(D(l), D(l + 1));
+        up(D0(), D(1));
     }
     {
         const LevelArgs &a = B.L[0].a;
@@ -1888,6 +1956,23 @@ bool launch_sweep_fused<double>(hipStream_t s, const Level &L, const double *uin
     return false;
 }
 
+template <class T, int TOP>
+static void bottom_lds(hipStream_t s, const Bottom<T> &B, const BottomLds &O, size_t bytes) {
+    // the dynamic-LDS limit is raised once per device (the contexts of one
+    // process may sit on several)
+    static std::atomic<unsigned long long> done{0};
+    int dev = 0;
+    DWP_HIP(hipGetDevice(&dev));
+    if (dev < 0 || dev >= 64) fail(DWP_EINVAL, "internal: device index out of range");
+    if (!(done.load() >> dev & 1)) {
+        DWP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_vcycle_bottom_lds<T, TOP>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)BOTTOM_LDS_BYTES));
+        done.fetch_or(1ull << dev);
+    }
+    k_vcycle_bottom_lds<T, TOP><<<1, 1024, bytes, s>>>(B, O);
+    DWP_LAUNCH_CHECK();
+}
+
 template <class T>
 void launch_vcycle_bottom(hipStream_t s, const std::vector<Level *> &levels, size_t l0, int pre, int post,
                           int coarse_sweeps) {
@@ -1909,35 +1994,32 @@ void launch_vcycle_bottom(hipStream_t s, const std::vector<Level *> &levels, siz
     B.pre = pre;
     B.post = post;
     B.coarse = coarse_sweeps;
-    // LDS layout of the whole bottom set, if it fits one workgroup's LDS
-    BottomLds O{};
-    size_t at = 0;
-    for (int l = 0; l < B.nl; ++l) {
-        const Level &L = *levels[l0 + l];
-        const size_t ng = L.n_ghosted(), ni = L.n_interior();
-        O.off[4 * l] = (int)at; at += ng;
-        O.off[4 * l + 1] = (int)at; at += ni;
-        O.off[4 * l + 2] = (int)at; at += ni;
-        O.off[4 * l + 3] = (int)at; at += ng;
-        at = (at + 3) / 4 * 4;  // keep every array 16-byte aligned
-    }
-    const size_t bytes = at * sizeof(T);
-    if (bytes <= BOTTOM_LDS_BYTES) {
-        // the dynamic-LDS limit is raised once per device (the contexts of one
-        // process may sit on several)
-        static bool attr_set[64] = {false};
-        int dev = 0;
-        DWP_HIP(hipGetDevice(&dev));
-        if (dev < 0 || dev >= 64) fail(DWP_EINVAL, "internal: device index out of range");
-        if (!attr_set[dev]) {
-            DWP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_vcycle_bottom_lds<T>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)BOTTOM_LDS_BYTES));
-            attr_set[dev] = true;
+    // LDS layout of the bottom set: everything if it fits one workgroup's LDS,
+    // else without the first level's residual, else without its f either (the
+    // coarsest level needs no residual; 16-bit neighbour indices bound the
+    // coarsest level's ghosted size, which the level limit keeps far below)
+    for (int top = 0; top < 3; ++top) {
+        BottomLds O{};
+        size_t at = 0;
+        auto put = [&](int slot, size_t n) {
+            O.off[slot] = (int)at;
+            at = (at + n + 3) / 4 * 4;  // keep every array 16-byte aligned
+        };
+        for (int l = 0; l < B.nl; ++l) {
+            const Level &L = *levels[l0 + l];
+            put(4 * l, L.n_ghosted());
+            put(4 * l + 3, L.n_ghosted());
+            if (l > 0 || top < 2) put(4 * l + 1, L.n_interior());
+            if (l + 1 < B.nl && (l > 0 || top < 1)) put(4 * l + 2, L.n_interior());
         }
-        k_vcycle_bottom_lds<T><<<1, 1024, bytes, s>>>(B, O);
-    } else {
-        k_vcycle_bottom<T><<<1, 1024, 0, s>>>(B);
+        const size_t bytes = at * sizeof(T);
+        if (bytes > BOTTOM_LDS_BYTES) continue;
+        if (top == 0) bottom_lds<T, 0>(s, B, O, bytes);
+        else if (top == 1) bottom_lds<T, 1>(s, B, O, bytes);
+        else bottom_lds<T, 2>(s, B, O, bytes);
+        return;
     }
+    k_vcycle_bottom<T><<<1, 1024, 0, s>>>(B);
     DWP_LAUNCH_CHECK();
 }
 
