@@ -47,6 +47,13 @@ struct DevBuf {
 };
 
 // ----------------------------------------------------------------------------
+// Tiling of a coarsest level's cooperative sweeps (k_coarse_coop): K = 0: none fits.
+struct CoopPlan {
+    int elem = 0;                 // bytes of the element type it was made for, 0: not yet
+    int ty = 0, tz = 0, bym = 0, bzm = 0, K = 0, H = 0, nt = 0;
+    size_t bytes = 0;
+};
+
 // One level of the wet-slab hierarchy.  Arrays of the unknowns and of eps hold
 // nw + 2 planes: plane 0 and plane nw + 1 are the Dirichlet planes next to the
 // slab (zero for the correction, the neighbouring node eps for eps); plane
@@ -61,6 +68,7 @@ struct Level {
     DevBuf u2;                    // second copy for out-of-place sweeps
     DevBuf f;                     // nw planes, T
     DevBuf r;                     // nw planes, T (residual scratch)
+    mutable CoopPlan coop;
     size_t n_interior() const { return plane * (size_t)nw; }
     size_t n_ghosted() const { return plane * (size_t)(nw + 2); }
 };
@@ -193,6 +201,8 @@ struct dwp_ctx {
     double background = 0.0;      // uniform background of the last order-6 solve
     double first_cycle_red = -1.0;  // residual reduction of the last solve's first cycle (< 0: none yet)
     dwp::PhaseTimer phases;       // phase timers of the solve in progress
+    dwp::DevBuf coop_halo;        // face words of the coarsest level's cooperative sweeps
+    unsigned coop_tag = 0;        // and the last step number used in them
     dwp::DevBuf bw_rhs, bw_lam;   // adjoint right-hand side and solution of dwp_backward
 };
 
@@ -283,7 +293,17 @@ bool launch_sweep_fused(hipStream_t s, const Level &L, const T *uin, T *uout, in
 template <class T>
 void launch_vcycle_bottom(hipStream_t s, const std::vector<Level *> &levels, size_t l0, int pre, int post,
                           int coarse_sweeps);
+// `sweeps` sweeps (colour 0 first) of a level's u in one cooperative launch on
+// many workgroups, which exchange their tiles' faces through `halo` (words
+// numbered from `tag` on); false, with nothing launched, where no tiling fits
+// or the stream is being captured
+template <class T>
+bool launch_coarse_coop(hipStream_t s, const Level &L, int sweeps, bool zero_in, DevBuf &halo, unsigned &tag);
+constexpr int COOP_MIN_SWEEPS = 8;
 constexpr size_t BOTTOM_MAX_POINTS = 8192;     // levels this small (and below) go to the bottom kernel
+// points whose sweeps the bottom kernel keeps in registers (1024 threads, two
+// points of a colour each in float64, three in float32)
+template <class T> constexpr size_t BOTTOM_REG_POINTS = sizeof(T) == 4 ? 6144 : 4096;
 constexpr size_t BOTTOM_LDS_BYTES = 160 * 1024;  // the bottom set runs out of LDS when it fits this
 constexpr size_t FUSED_MIN_POINTS = 1u << 20;  // levels this large use the fused sweep
 constexpr size_t BAND_MIN_POINTS = 1u << 14;   // the row-band fused sweep from this size where it fits

@@ -1425,6 +1425,235 @@ __global__ void __launch_bounds__(1024) k_vcycle_bottom_lds(Bottom<T> B, BottomL
     }
 }
 
+// ---------------------------------------------------------------- coarsest level on many workgroups
+// All `sweeps` red-black sweeps of a level in one cooperative launch.  A level
+// that cannot be coarsened further (x or y = 2 mod 4) but is too large for one
+// workgroup used to take one launch per sweep, 7-10 us each for 36 000 -
+// 330 000 points: latency (the launch, a march of dependent plane loads), not
+// traffic.  Here every workgroup keeps a tile of whole rows (rows [j0, j1) of
+// planes [k0, k1)) for all sweeps: u with a one-cell halo in LDS, the face
+// weights, reciprocal diagonals and right-hand sides of its points in
+// registers (K points of each colour per thread), and after each colour only
+// the tile's outer faces travel.  A face value crosses in self-describing
+// 64-bit words, 32 bits of value under 32 bits of step number (two words per
+// float64), written and polled with relaxed device-scope atomics: a word whose
+// step number is right holds the right value, so there is no flag to order
+// against and no fence.  Two copies of the words alternate: a workgroup can
+// write step s + 2 only after its neighbours have sent step s + 1, which they
+// do after they have read step s.  All workgroups are resident (cooperative
+// launch, at most one per CU), so every wait ends; a wait that still exceeds
+// COOP_SPINS polls gives up and puts NaN into u, which the Krylov solver
+// reports as a non-finite basis.  Measured in the solve (float64, 64 sweeps,
+// kernel trace): 54 x 48 x 127 points 217 us against 64 launches of 10.0 us,
+// 18 x 18 x 111 points 135 us against 64 of 7.1 us; what bounds it is the
+// exchange, 0.9 us a colour with few words.  Words are laid out so that a
+// wavefront's loads and stores are contiguous (the two words of a float64
+// apart: side by side they took 1.5 times as long).  Same operations on the
+// same values as the colour passes.
+// units of 64 clocks before the first poll: a word takes about 0.9 us to cross,
+// and polls that come too early only load the fabric (54 x 48 x 127 points: 0 units
+// 1.15 times the whole gradient's time at 16; 12: 1.05; 24: 1.02)
+constexpr int COOP_WAIT = 16;
+constexpr int COOP_SPINS = 1 << 20;
+template <class T> struct CoopArgs {
+    T *u;                             // ghosted
+    const T *e, *f;
+    LevelArgs a;
+    int sweeps, zero_in;
+    int ty, tz, bym, bzm;             // tile counts, largest tile extents
+    unsigned long long *halo;         // [2][tiles][face words]
+    unsigned tag;                     // step numbers of this launch: tag + 1 ..
+};
+
+template <class T> struct CoopWord;
+template <> struct CoopWord<float> {
+    static constexpr int N = 1;
+    static __device__ __forceinline__ unsigned part(float v, int) { return __float_as_uint(v); }
+    static __device__ __forceinline__ float join(const unsigned *p) { return __uint_as_float(p[0]); }
+};
+template <> struct CoopWord<double> {
+    static constexpr int N = 2;
+    static __device__ __forceinline__ unsigned part(double v, int q) {
+        return q ? (unsigned)__double2hiint(v) : (unsigned)__double2loint(v);
+    }
+    static __device__ __forceinline__ double join(const unsigned *p) { return __hiloint2double((int)p[1], (int)p[0]); }
+};
+
+// K points of each colour and H face words per thread, NT threads.  A thread
+// sends the face values it computed itself, straight from its registers (both
+// colours of a pair of points sit in the same words), and receives H words
+// into the halo; one barrier per colour follows.
+template <class T, int K, int H, int NT>
+__global__ void __launch_bounds__(NT) k_coarse_coop(CoopArgs<T> A) {
+    extern __shared__ __align__(16) unsigned char coop_lds[];
+    T *lu = reinterpret_cast<T *>(coop_lds);
+    constexpr int NWD = CoopWord<T>::N;
+    const int nx = A.a.nx, ny = A.a.ny, nw = A.a.nw, half = nx / 2, plane = nx * ny;
+    const int ty = blockIdx.x % A.ty, tz = blockIdx.x / A.ty;
+    const int j0 = ty * ny / A.ty, j1 = (ty + 1) * ny / A.ty, by = j1 - j0;
+    const int k0 = tz * nw / A.tz, k1 = (tz + 1) * nw / A.tz, bz = k1 - k0;
+    const bool split = A.ty > 1;      // rows split: halo rows 0 and by + 1; else y wraps inside the tile
+    const int jb = split ? 1 : 0, nr = by + 2 * jb, lplane = nr * nx;
+    const int tid = threadIdx.x;
+    // u of the tile and its halo (corners too, which nothing reads)
+    for (int q = tid; q < (bz + 2) * lplane; q += NT) {
+        const int i = q % nx, r = (q / nx) % nr, pl = q / lplane;
+        int j = j0 - jb + r;
+        j = j < 0 ? j + ny : (j >= ny ? j - ny : j);
+        lu[q] = A.zero_in ? T(0) : A.u[(size_t)(k0 + pl) * plane + j * nx + i];
+    }
+    // places of the four faces' words of a tile: z low, z high, y low, y high
+    const int fz = half * A.bym, fy = half * A.bzm, stride = 2 * (fz + fy);
+    const int copy = A.ty * A.tz * stride * NWD;
+    // this thread's points, and where it sends each pair (negative: nowhere)
+    const int per = half * by * bz;
+    const T cx = cxv<T>(A.a, 0), cy = cxv<T>(A.a, 1), cz = cxv<T>(A.a, 2);
+    T w[2][K][6], rd[2][K], fv[2][K];
+    int g[2][K], ox[2][K], oy[2][K], snd[K][4];
+#pragma unroll
+    for (int m = 0; m < K; ++m) {
+        const int q = min(tid + m * NT, per - 1);
+        const int t = q % half, r = (q / half) % by, pl = q / (half * by);
+        const int j = j0 + r, k = k0 + pl;
+        const bool mine = tid + m * NT < per;
+        const int tile0 = (int)blockIdx.x * stride * NWD;
+        snd[m][0] = mine && pl == 0 && tz > 0 ? tile0 + r * half + t : -1;
+        snd[m][1] = mine && pl == bz - 1 && tz + 1 < A.tz ? tile0 + fz + r * half + t : -1;
+        snd[m][2] = mine && split && r == 0 ? tile0 + 2 * fz + pl * half + t : -1;
+        snd[m][3] = mine && split && r == by - 1 ? tile0 + 2 * fz + fy + pl * half + t : -1;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int i = 2 * t + ((j + k + c) & 1);
+            const size_t ge = (size_t)(k + 1) * plane;
+            const T *ep = A.e + ge;
+            const int c0 = j * nx + i;
+            const T e0 = ep[c0];
+            T *ww = w[c][m];
+            ww[0] = cx * (e0 + ep[j * nx + wrap_p(i, nx)]);
+            ww[1] = cx * (e0 + ep[j * nx + wrap_m(i, nx)]);
+            ww[2] = cy * (e0 + ep[wrap_p(j, ny) * nx + i]);
+            ww[3] = cy * (e0 + ep[wrap_m(j, ny) * nx + i]);
+            ww[4] = cz * (e0 + ep[plane + c0]);
+            ww[5] = cz * (e0 + A.e[ge - plane + c0]);
+            rd[c][m] = gs_recip(T(0.5) * (ww[0] + ww[1] + ww[2] + ww[3] + ww[4] + ww[5]));
+            fv[c][m] = A.f[(size_t)k * plane + c0];
+            const int lr = r + jb, row = ((pl + 1) * nr + lr) * nx, gi = row + i;
+            const int rp = split ? lr + 1 : wrap_p(lr, ny), rm = split ? lr - 1 : wrap_m(lr, ny);
+            g[c][m] = gi;
+            ox[c][m] = (row + wrap_p(i, nx)) | ((row + wrap_m(i, nx)) << 16);
+            oy[c][m] = (gi + (rp - lr) * nx) | ((gi + (rm - lr) * nx) << 16);
+        }
+    }
+    // the words this thread receives: place, and the LDS index of the pair
+    // (2 t, 2 t + 1) with the colour parity of its row in bit 0 (it is even)
+    const int nzf = half * by, nyf = split ? half * bz : 0;
+    int rl[H], rw[H];
+    bool on[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        const int q = tid + h * NT;
+        on[h] = q < 2 * (nzf + nyf);
+        rl[h] = rw[h] = 0;
+        if (!on[h]) continue;
+        const bool zf = q < 2 * nzf;
+        const int qq = zf ? q : q - 2 * nzf, n1 = zf ? nzf : nyf;
+        const bool hi = qq >= n1;
+        const int x = hi ? qq - n1 : qq, t = x % half, o = x / half;  // o: row (z faces) or plane (y faces)
+        int nt, rj, rk, rp, rr, opp;  // sending tile; global row and plane, local plane and row; its face
+        if (zf) {
+            const int zn = tz + (hi ? 1 : -1);
+            on[h] = zn >= 0 && zn < A.tz;
+            nt = zn * A.ty + ty;
+            rj = j0 + o;
+            rk = hi ? k1 : k0 - 1;
+            rr = o + jb;
+            rp = hi ? bz + 1 : 0;
+            opp = hi ? 0 : fz;
+        } else {
+            nt = tz * A.ty + (hi ? (ty + 1 == A.ty ? 0 : ty + 1) : (ty == 0 ? A.ty - 1 : ty - 1));
+            rk = k0 + o;
+            rj = hi ? (j1 == ny ? 0 : j1) : (j0 == 0 ? ny - 1 : j0 - 1);
+            rp = o + 1;
+            rr = hi ? by + 1 : 0;
+            opp = 2 * fz + (hi ? 0 : fy);
+        }
+        rl[h] = ((rp * nr + rr) * nx + 2 * t) | ((rj + rk + 2) & 1);
+        rw[h] = on[h] ? nt * stride * NWD + opp + x : 0;
+    }
+    bool lost = false;
+    __syncthreads();
+    const int steps = 2 * A.sweeps;
+    for (int st = 0; st < steps; st += 2) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const bool last = st + c + 1 == steps;  // nothing reads the last colour's halo
+            const unsigned tag = A.tag + (unsigned)(st + c + 1);
+            const unsigned long long tagw = (unsigned long long)tag << 32;
+            unsigned long long *buf = A.halo + (size_t)c * copy;
+#pragma unroll
+            for (int m = 0; m < K; ++m)
+                if (tid + m * NT < per) {
+                    const T *ww = w[c][m];
+                    const int gi = g[c][m], x2 = ox[c][m], y2 = oy[c][m];
+                    const T off = T(0.5) * (ww[0] * lu[x2 & 0xFFFF] + ww[1] * lu[(unsigned)x2 >> 16] +
+                                            ww[2] * lu[y2 & 0xFFFF] + ww[3] * lu[(unsigned)y2 >> 16] +
+                                            ww[4] * lu[gi + lplane] + ww[5] * lu[gi - lplane]);
+                    const T v = (off - fv[c][m]) * rd[c][m];
+                    if (!last) {
+#pragma unroll
+                        for (int d = 0; d < 4; ++d)
+                            if (snd[m][d] >= 0)
+#pragma unroll
+                                for (int q = 0; q < NWD; ++q)
+                                    __hip_atomic_store(buf + snd[m][d] + q * stride, tagw | CoopWord<T>::part(v, q),
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                    lu[gi] = v;
+                }
+            if (!last) {
+                unsigned part[H][NWD];
+                bool all = lost;
+                __builtin_amdgcn_s_sleep(COOP_WAIT);
+                for (int spin = 0; !all; ++spin) {
+                    if (spin) __builtin_amdgcn_s_sleep(2);
+                    all = true;
+                    unsigned long long x[H][NWD];
+#pragma unroll
+                    for (int h = 0; h < H; ++h)
+#pragma unroll
+                        for (int q = 0; q < NWD; ++q)
+                            x[h][q] = on[h] ? __hip_atomic_load(buf + rw[h] + q * stride, __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_AGENT)
+                                            : tagw;
+#pragma unroll
+                    for (int h = 0; h < H; ++h)
+#pragma unroll
+                        for (int q = 0; q < NWD; ++q) {
+                            all = all && (unsigned)(x[h][q] >> 32) == tag;
+                            part[h][q] = (unsigned)x[h][q];
+                        }
+                    if (spin >= COOP_SPINS && !all) { lost = true; break; }
+                }
+#pragma unroll
+                for (int h = 0; h < H; ++h)
+                    if (on[h]) lu[rl[h] ^ c] = lost ? T(__builtin_nanf("")) : CoopWord<T>::join(part[h]);
+            }
+            __syncthreads();
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int m = 0; m < K; ++m) {
+            const int q = tid + m * NT;
+            if (q < per) {
+                const int t = q % half, r = (q / half) % by, pl = q / (half * by);
+                const int j = j0 + r, k = k0 + pl, i = 2 * t + ((j + k + c) & 1);
+                A.u[(size_t)(k + 1) * plane + j * nx + i] = lu[g[c][m]];
+            }
+        }
+}
+
 inline int grid1d(size_t n, int threads = 256) {
     size_t b = (n + threads - 1) / threads;
     if (b > 16384) b = 16384;
@@ -2024,6 +2253,76 @@ void launch_vcycle_bottom(hipStream_t s, const std::vector<Level *> &levels, siz
 }
 
 template <class T>
+void launch_zero(hipStream_t s, T *x, size_t n);
+// Tiles of k_coarse_coop for a level: rows split ty ways, planes tz ways, at
+// most one tile per CU.  The variant (points of a colour, face words, threads)
+// is the first of COOP_VARIANTS that some split fits: fewer points and words
+// per thread make a colour faster (a gradient step over 54 x 48 x 127 points
+// in float64: 28.4 ms with one of each on 1024 threads, 28.9 with two on 512,
+// 36.1 with three); among the splits, the one with the fewest words to exchange
+// per tile.
+// Searched once per level and type.
+struct CoopVariant { int K, H, nt; };
+constexpr CoopVariant COOP_VARIANTS[] = {{1, 1, 512}, {1, 1, 1024}, {2, 2, 512}, {3, 2, 512}};
+template <class T> static const CoopPlan &coop_plan(const Level &L) {
+    CoopPlan &best = L.coop;
+    if (best.elem == (int)sizeof(T)) return best;
+    best = CoopPlan{};
+    best.elem = sizeof(T);
+    const int half = L.nx / 2, cus = cu_count();
+    for (const CoopVariant &v : COOP_VARIANTS) {
+        long fewest = -1;
+        for (int ty = 1; ty <= std::min(L.ny / 2, cus); ++ty)
+            for (int tz = 1; tz <= std::min(L.nw, cus / ty); ++tz) {
+                const int bym = (L.ny + ty - 1) / ty, bzm = (L.nw + tz - 1) / tz;
+                const long words = 2L * half * (bym + (ty > 1 ? bzm : 0));
+                const size_t elems = (size_t)(bzm + 2) * (bym + (ty > 1 ? 2 : 0)) * L.nx;
+                if ((long)half * bym * bzm > (long)v.K * v.nt || words > (long)v.H * v.nt) continue;
+                if (sizeof(T) * elems > BOTTOM_LDS_BYTES || elems > 65536) continue;
+                if (fewest >= 0 && words >= fewest) continue;
+                fewest = words;
+                best = CoopPlan{(int)sizeof(T), ty, tz, bym, bzm, v.K, v.H, v.nt, sizeof(T) * elems};
+            }
+        if (best.K) break;
+    }
+    return best;
+}
+template <class T, int K, int H, int NT> static bool coop_launch(hipStream_t s, CoopArgs<T> &A, const CoopPlan &q) {
+    const void *fn = reinterpret_cast<const void *>(&k_coarse_coop<T, K, H, NT>);
+    if (occupancy(fn, NT, q.bytes) < 1) return false;
+    void *args[] = {&A};
+    DWP_HIP(hipLaunchCooperativeKernel(fn, dim3(q.ty * q.tz), dim3(NT), args, (unsigned)q.bytes, s));
+    return true;
+}
+template <class T>
+bool launch_coarse_coop(hipStream_t s, const Level &L, int sweeps, bool zero_in, DevBuf &halo, unsigned &tag) {
+    // a captured graph would replay the step numbers of its capture
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    DWP_HIP(hipStreamIsCapturing(s, &cap));
+    if (cap != hipStreamCaptureStatusNone) return false;
+    const CoopPlan &q = coop_plan<T>(L);
+    if (q.K == 0) return false;
+    const int half = L.nx / 2;
+    const size_t words = (size_t)2 * q.ty * q.tz * 2 * half * (q.bym + q.bzm) * CoopWord<T>::N;
+    const unsigned steps = 2u * (unsigned)sweeps;
+    // the words' step numbers only ever grow; a new buffer, or numbers about to
+    // wrap, start from zeroed words
+    const bool fresh = halo.bytes < 8 * words || tag > 0x7FFFFFFFu - steps;
+    if (fresh) {
+        halo.alloc(8 * words);
+        launch_zero<double>(s, halo.as<double>(), halo.bytes / 8);
+        tag = 0;
+    }
+    CoopArgs<T> A{L.u.as<T>(), L.eps.as<T>(), L.f.as<T>(), level_args(L), sweeps, zero_in ? 1 : 0,
+                  q.ty, q.tz, q.bym, q.bzm, halo.as<unsigned long long>(), tag};
+    const bool ok = q.K == 3 ? coop_launch<T, 3, 2, 512>(s, A, q)
+                    : q.K == 2 ? coop_launch<T, 2, 2, 512>(s, A, q)
+                    : q.nt == 1024 ? coop_launch<T, 1, 1, 1024>(s, A, q) : coop_launch<T, 1, 1, 512>(s, A, q);
+    if (ok) tag += steps;
+    return ok;
+}
+
+template <class T>
 void launch_zero(hipStream_t s, T *x, size_t n) {
     k_zero<T><<<grid1d(n), 256, 0, s>>>(x, n);
     DWP_LAUNCH_CHECK();
@@ -2046,6 +2345,7 @@ void launch_zero(hipStream_t s, T *x, size_t n) {
     template void launch_prolong_add<T>(hipStream_t, const Level &, const Level &);                   \
     template void launch_coarsen_eps<T>(hipStream_t, const Level &, const Level &);                   \
     template void launch_zero<T>(hipStream_t, T *, size_t);                                          \
+    template bool launch_coarse_coop<T>(hipStream_t, const Level &, int, bool, DevBuf &, unsigned &); \
     template void launch_vcycle_bottom<T>(hipStream_t, const std::vector<Level *> &, size_t, int, int, int);
 DWP_INST(float)
 DWP_INST(double)

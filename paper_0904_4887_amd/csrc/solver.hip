@@ -356,6 +356,20 @@ bool vcycle(dwp_ctx *c, size_t l, bool u_unset, T *zadd) {
     bool zero_in = (l > 0 || u_unset) && (coarsest || c->opts.pre > 0);
     if (u_unset && !(fused && zero_in))
         PROF(c, PG_WET, ts * (double)L.n_ghosted(), launch_zero<T>(s, L.u.as<T>(), L.n_ghosted()));
+    // a coarsest level beyond the single-workgroup bottom's registers sweeps on
+    // many workgroups in one cooperative launch, which costs about 20 us more
+    // than a plain one: worth it from COOP_MIN_SWEEPS sweeps on (a sweep takes
+    // 2-3.5 us in it, one launch per sweep 7-10 us)
+    if (coarsest && !six && c->opts.smoother == 1 && c->opts.coarse_sweeps >= COOP_MIN_SWEEPS &&
+        npts > BOTTOM_REG_POINTS<T>) {
+        const int ev = c->prof.begin(s, sg);
+        const bool zero = l > 0 || u_unset;
+        const bool ok = launch_coarse_coop<T>(s, L, c->opts.coarse_sweeps, zero, c->coop_halo, c->coop_tag);
+        if (ok) {
+            c->prof.end(s, ev, sg, 2.0 * pass_bytes * c->opts.coarse_sweeps);
+            return false;
+        }
+    }
     if (l >= p.bottom) {
         double nb = 0.0;
         for (size_t q = l; q < p.levels.size(); ++q) nb += (double)p.levels[q]->n_interior();

@@ -297,15 +297,19 @@ def _rb_sweeps(f, eps, h, sweeps):
 
 # the sizes take the single-level bottom kernel through one, two and three points
 # of a colour per thread and past its registers, with everything in LDS, with f
-# outside and (the wide thin slabs) out of global memory
-@pytest.mark.parametrize("n,planes", [((8, 8, 16), 3), ((12, 18, 16), 9), ((18, 16, 32), 13), ((24, 16, 32), 15),
-                                      ((32, 16, 32), 16), ((64, 64, 16), 2 + 1)])
+# outside and (the wide thin slabs) out of global memory; 9 sweeps of a level
+# beyond those registers take the cooperative kernel, with tiles of one to three
+# points of a colour per thread, rows whole and split, uneven tiles, one plane a tile
+@pytest.mark.parametrize("n,planes,sweeps", [
+    ((8, 8, 16), 3, 7), ((12, 18, 16), 9, 7), ((18, 16, 32), 13, 7), ((24, 16, 32), 15, 7), ((32, 16, 32), 16, 7),
+    ((64, 64, 16), 3, 7), ((18, 16, 32), 25, 9), ((18, 18, 128), 111, 9), ((54, 48, 64), 41, 64), ((64, 96, 16), 3, 9),
+    ((54, 108, 162), 127, 9), ((8, 8, 512), 400, 8), ((162, 16, 32), 20, 9)])
 @pytest.mark.parametrize("precision", [0, 1])
-def test_coarsest_sweeps_match_written_out_sweeps(torch, n, planes, precision):
+def test_coarsest_sweeps_match_written_out_sweeps(torch, n, planes, sweeps, precision):
     from paper_0904_4887_amd import binding as B
     L = (0.3 * n[0], 0.25 * n[1], 0.4 * n[2])
     lo = L[2] * (n[2] - planes) / n[2]
-    opts = dict(precision=precision, z_wet_lo=lo, z_wet_hi=L[2], max_levels=1, coarse_sweeps=7, cycles=1)
+    opts = dict(precision=precision, z_wet_lo=lo, z_wet_hi=L[2], max_levels=1, coarse_sweeps=sweeps, cycles=2)
     pl = B.plan(n, L, **opts)
     k0, nw = pl["k_w0"], pl["levels"][0][2]
     assert len(pl["levels"]) == 1
@@ -318,10 +322,44 @@ def test_coarsest_sweeps_match_written_out_sweeps(torch, n, planes, precision):
     wet = [(k0 + q) % n[2] for q in range(nw)]
     ext = [(k0 - 1 + q) % n[2] for q in range(nw + 2)]
     ref = dry.copy()
-    ref[wet] += _rb_sweeps(rw[wet], eps[ext], s.h, 7)
+    # two cycles of one level: the second goes on from the first one's values
+    ref[wet] += _rb_sweeps(rw[wet], eps[ext], s.h, 2 * sweeps)
+    assert _rel(_host(s.apply_split(_dev(torch, r))), z) == 0.0
     # float32: the level's values and updates round at 6e-8; the bar of the
     # other bottom test
     assert _rel(z, ref) <= (1e-12 if precision == 0 else 1e-4)
+
+
+def test_cooperative_sweeps_from_two_threads(torch):
+    """Two contexts on streams of their own, driven by two threads, each with a
+    coarsest level that takes the cooperative kernel on every CU: the results
+    are those of the same calls one after the other."""
+    import threading
+    n, L = (108, 96, 96), (11.8, 11.8, 40.0)
+    eps, r = W.random_fields(n, 37)
+    de, dr = _dev(torch, eps), _dev(torch, r)
+    torch.cuda.synchronize()
+    out, alone = [[], []], None
+
+    def work(q):
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            s = _solver(torch, n, L, z_wet_lo=0.3 * L[2], z_wet_hi=L[2])
+            s.set_epsilon(de)
+            z = [s.apply_split(dr) for _ in range(6)]
+            st.synchronize()
+            out[q] = [_host(t) for t in z]
+
+    work(0)
+    alone = out[0][0]
+    threads = [threading.Thread(target=work, args=(q,)) for q in (0, 1)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for z in out[0] + out[1]:
+        assert np.array_equal(z, alone)
+    assert len(out[1]) == 6
 
 
 @pytest.mark.parametrize("n", [(24, 36, 48), (96, 96, 192), (192, 192, 384), (256, 256, 32), (18, 54, 48),
