@@ -359,9 +359,12 @@ bool vcycle(dwp_ctx *c, size_t l, bool u_unset, T *zadd) {
     // a coarsest level beyond the single-workgroup bottom's registers sweeps on
     // many workgroups in one cooperative launch, which costs about 20 us more
     // than a plain one: worth it from COOP_MIN_SWEEPS sweeps on (a sweep takes
-    // 2-3.5 us in it, one launch per sweep 7-10 us)
+    // 2-3.5 us in it, one launch per sweep 7-10 us).  In float32 only where the
+    // sweeps would otherwise be colour passes, which it equals bit for bit: the
+    // fused sweeps round differently in the last place, and in mixed precision
+    // that can move a solve's last iteration across its tolerance.
     if (coarsest && !six && c->opts.smoother == 1 && c->opts.coarse_sweeps >= COOP_MIN_SWEEPS &&
-        npts > BOTTOM_REG_POINTS<T>) {
+        npts > BOTTOM_REG_POINTS<T> && (sizeof(T) == 8 || !fused)) {
         const int ev = c->prof.begin(s, sg);
         const bool zero = l > 0 || u_unset;
         const bool ok = launch_coarse_coop<T>(s, L, c->opts.coarse_sweeps, zero, c->coop_halo, c->coop_tag);
