@@ -12,6 +12,9 @@
 // is periodic and at least 8 long, so a shift of up to 3 wraps at most once.
 #include "dwp_internal.h"
 
+#include <algorithm>
+#include <mutex>
+
 namespace dwp {
 
 namespace {
@@ -81,127 +84,343 @@ __global__ void __launch_bounds__(SX *SY) k_d1eps(Grid6 g, const double *__restr
 }
 
 // LDS-tiled form of the operator, its transpose and their residual forms.  A
-// block owns a 64 x 4 column tile and marches up a chunk of Z6 planes; at each
-// plane it stages the tile plus a 3-cell halo in x and y in LDS and keeps the
-// z neighbours (k-3 .. k+3) of its own column in registers, so that every
-// input element is read from memory about once per plane instead of once per
-// stencil point.
-//   forward:    LDS holds x;              registers hold x at k-3..k+3.
+// block owns a tile of ty rows of wp pairs of points (one 2-wide vector per
+// thread; wp divides nx / 2 and ty divides ny, so no tile overhangs) for a
+// chunk of kc planes.  It keeps the z neighbours (k - 3 .. k + 3) of its own
+// points in registers and stages each plane with a halo of 4 columns and 3 rows
+// in LDS (two slots): its own points from the registers, so that only the halo
+// is loaded again.  Loads are issued one plane step ahead of their use; one
+// barrier per step.
+//   forward:    LDS and registers hold x and, in float64, eps; G = D1 eps is
+//               formed from it, with the operations of k_d1eps, so that 24 bytes
+//               per point move instead of 48 with G read back.  (On float32
+//               vectors G is read: formed from eps in float32 it would lose
+//               digits to cancellation.)
 //   transposed: LDS holds eps y, Gx y, Gy y (the products the transpose
-//               differentiates);         registers hold eps y and Gz y.
+//               differentiates); registers hold eps y and Gz y.  G is read: it
+//               is needed at the neighbours, where it would take eps 6 cells out.
 // MODE 0: out = op x;  1: out = b - op x;  2: out (wet slab plane q, type T) =
-// b - op x at box plane (k_w0 + q) mod nz.
-constexpr int T6X = 64, T6Y = 4, H6 = 3;
-constexpr int L6X = T6X + 2 * H6, L6Y = T6Y + 2 * H6, L6N = L6X * L6Y;
-constexpr int T6N = T6X * T6Y;
-constexpr int T6L = (L6N + T6N - 1) / T6N;  // tile loads per thread
-constexpr int Z6 = 16;                      // planes per block
+// b - op x at box plane (k_w0 + q) mod nz.  AL: the box arrays are 16-byte
+// aligned (a caller's may be aligned to 8 only: pairs are then loaded in halves).
+// Bound by HBM, LDS reads and float64 arithmetic alike at large grids (a plane
+// step spends about a microsecond of each per CU), by the latency of the steps
+// at small ones.  A6 at 192 x 192 x 384 in float64: 176 us with 64 x 4 tiles, two
+// barriers and unhidden loads a plane and G read; 86 us so.  On float32 vectors
+// at 96 x 96 x 192 (kernel trace): 30.4 -> 14.0 us, transposed 36.2 -> 23.2 us.
+constexpr int H6X = 4, H6Y = 3;             // halo columns (pair-aligned) and rows
+constexpr int OP6_NT_FWD = 768, OP6_NT_TRANS = 512;  // most threads (168 and 256 registers)
 
-// TX, TE: storage of x and of eps, G (float32 for a float32 Krylov vector); the
-// arithmetic is float64 either way
-template <int MODE, bool TRANS, class T, class TX = double, class TE = double>
-__global__ void __launch_bounds__(T6N)
-k_op6_tile(Grid6 g, int k_w0, int nplanes, int tiles_x, int tiles_y, const TX *__restrict__ x,
-           const TE *__restrict__ eps, const TE *__restrict__ G, const double *__restrict__ b,
-           T *__restrict__ out) {
-    __shared__ double s0[L6N], s1[TRANS ? L6N : 1], s2[TRANS ? L6N : 1];
+struct Op6Shape {
+    int k_w0, nplanes, wp, ty, tiles_x, tiles_y, kc, nb;
+};
+
+typedef double d2v __attribute__((ext_vector_type(2)));
+typedef float f2v __attribute__((ext_vector_type(2)));
+
+template <bool AL> __device__ __forceinline__ d2v ldp(const double *p) {
+    if constexpr (AL) return *(const d2v *)p;
+    else return d2v{p[0], p[1]};
+}
+template <bool AL> __device__ __forceinline__ d2v ldp(const float *p) {
+    const f2v v = *(const f2v *)p;  // the library's own arrays only
+    return d2v{(double)v[0], (double)v[1]};
+}
+template <bool AL> __device__ __forceinline__ void stp(double *p, d2v v) {
+    if constexpr (AL) *(d2v *)p = v;
+    else { p[0] = v[0]; p[1] = v[1]; }
+}
+template <bool AL> __device__ __forceinline__ void stp(float *p, d2v v) {
+    *(f2v *)p = f2v{(float)v[0], (float)v[1]};
+}
+
+// Where a block and a thread stand: tile origin, planes, the thread's own pair
+// and its halo pair (in-plane element offset and LDS index, ylo: a row halo).
+struct Op6Pos {
+    int q0, q1, kb, own_l, halo_l, ls;
+    bool own, halo, ylo;
+    unsigned own_o, halo_o;
+};
+__device__ __forceinline__ bool op6_pos(const Grid6 &g, const Op6Shape &p, Op6Pos &t) {
+    // each XCD (hardware block b runs on XCD b mod 8) gets a run of neighbouring tiles
+    const int tile = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    if (tile >= p.nb) return false;
+    const int x0 = (tile % p.tiles_x) * 2 * p.wp, y0 = ((tile / p.tiles_x) % p.tiles_y) * p.ty;
+    t.q0 = (tile / (p.tiles_x * p.tiles_y)) * p.kc;
+    t.q1 = min(p.nplanes, t.q0 + p.kc);
+    t.ls = 2 * p.wp + 2 * H6X;  // LDS row length
     const int tid = threadIdx.x;
-    const int tile = blockIdx.x;
-    const int i0 = (tile % tiles_x) * T6X, j0 = ((tile / tiles_x) % tiles_y) * T6Y;
-    const int q0 = (tile / (tiles_x * tiles_y)) * Z6, q1 = min(nplanes, q0 + Z6);
-    const int lx = tid % T6X, ly = tid / T6X;
-    const int i = i0 + lx, j = j0 + ly;
-    const bool own = i < g.nx && j < g.ny;
-    const size_t cc = own ? (size_t)j * g.nx + i : 0;  // in-plane offset of this thread's node
-    const TE *Gx = G, *Gy = G + g.N, *Gz = G + 2 * g.N;
-    // in-plane offsets of this thread's tile loads (periodic, any tile overhang)
-    size_t lo[T6L];
-#pragma unroll
-    for (int m = 0; m < T6L; ++m) {
-        const int q = min(tid + T6N * m, L6N - 1);
-        const int xr = q % L6X, yr = q / L6X;
-        const int gx = ((i0 - H6 + xr) % g.nx + g.nx) % g.nx, gy = ((j0 - H6 + yr) % g.ny + g.ny) % g.ny;
-        lo[m] = (size_t)gy * g.nx + gx;
+    const int r = tid / p.wp, c = tid - r * p.wp;
+    t.own = r < p.ty;
+    const int rr = t.own ? r : 0;
+    t.own_o = (unsigned)((y0 + rr) * g.nx + x0 + 2 * c);
+    t.own_l = (rr + H6Y) * t.ls + H6X + 2 * c;
+    const int nhx = 4 * p.ty, nh = nhx + 2 * H6Y * p.wp;
+    t.halo = tid < nh;
+    const int h = t.halo ? tid : 0;
+    int x, y, lx, ly;
+    if (h < nhx) {  // two pairs left and two right of each row
+        const int side = h & 3;
+        ly = h >> 2;
+        lx = side < 2 ? 2 * side - 4 : 2 * p.wp + 2 * (side - 2);
+        t.ylo = false;
+    } else {        // three rows below and three above
+        const int q = h - nhx, row = q / p.wp;
+        ly = row < H6Y ? row - H6Y : p.ty + row - H6Y;
+        lx = 2 * (q - row * p.wp);
+        t.ylo = true;
     }
-    auto zplane = [&](int k) { return (size_t)(((k % g.nz) + g.nz) % g.nz) * g.plane; };
-    const int kb = MODE == 2 ? k_w0 : 0;
-    // z queues: a[d] and c[d] for plane k - 3 + d
-    double a[7], c[7];
-    auto zload = [&](int k, double &av, double &cv) {
-        const size_t o = zplane(k) + cc;
-        if (TRANS) {
-            const double y = (double)x[o];
-            av = (double)eps[o] * y;
-            cv = (double)Gz[o] * y;
-        } else {
-            av = (double)x[o];
-            cv = 0.0;
+    x = wrap(x0 + lx, g.nx);
+    y = wrap(y0 + ly, g.ny);
+    t.halo_o = (unsigned)(y * g.nx + x);
+    t.halo_l = (ly + H6Y) * t.ls + H6X + lx;
+    return true;
+}
+
+// ih sum_n A_n (f_{+n} - f_{-n}) and B_0 f_0 + sum_n B_n (f_{+n} + f_{-n})
+__device__ __forceinline__ double d1v(double ih, double m3, double m2, double m1, double p1, double p2, double p3) {
+    return ih * (A1 * (p1 - m1) + A2 * (p2 - m2) + A3 * (p3 - m3));
+}
+__device__ __forceinline__ double d2s(double m3, double m2, double m1, double c, double p1, double p2, double p3) {
+    return B0 * c + B1 * (p1 + m1) + B2 * (p2 + m2) + B3 * (p3 + m3);
+}
+// the seven values -3 .. 3 along x around each of a pair, f[e .. e + 6]
+struct Row8 {
+    double f[8];
+};
+__device__ __forceinline__ Row8 row8(const double *l, d2v c) {
+    const d2v a = *(const d2v *)(l - 4), b = *(const d2v *)(l - 2), d = *(const d2v *)(l + 2), e = *(const d2v *)(l + 4);
+    return Row8{{a[1], b[0], b[1], c[0], c[1], d[0], d[1], e[0]}};
+}
+
+// G: null to form G from eps (float64 eps, staged like x), else read at the point
+// with eps (float32 vectors: eps and G rounded to float32).
+template <int MODE, class T, class TX, class TE, bool AL>
+__global__ void __launch_bounds__(OP6_NT_FWD)
+k_op6_fwd(Grid6 g, Op6Shape p, const TX *__restrict__ x, const TE *__restrict__ eps, const TE *__restrict__ G,
+          const double *__restrict__ b, T *__restrict__ out) {
+    extern __shared__ __align__(16) double op6_lds[];
+    constexpr bool FORM = sizeof(TE) == 8;  // G is formed here
+    Op6Pos t;
+    if (!op6_pos(g, p, t)) return;
+    const int field = (p.ty + 2 * H6Y) * t.ls;
+    const int kb = MODE == 2 ? p.k_w0 : 0;
+    auto zp = [&](int k) { return (size_t)wrap(k >= g.nz ? k - g.nz : k, g.nz) * g.plane; };
+    // x (and eps) at planes k - 3 .. k + 3 and of the halo pair; with G read, eps and G at plane k
+    d2v xq[7], eq[FORM ? 7 : 1], hx{0, 0}, he{0, 0}, gq[FORM ? 1 : 3];
+    const int kf = kb + t.q0;
+#pragma unroll
+    for (int d = 0; d < 7; ++d) {
+        const size_t o = zp(kf - 3 + d) + t.own_o;
+        xq[d] = ldp<AL>(x + o);
+        if constexpr (FORM) eq[d] = ldp<true>(eps + o);
+    }
+    auto halo = [&](int k) {
+        if (t.halo) {
+            const size_t o = zp(k) + t.halo_o;
+            hx = ldp<AL>(x + o);
+            if constexpr (FORM) he = ldp<true>(eps + o);
         }
     };
-    const int kfirst = kb + q0;
+    auto stash = [&](int slot, d2v xv, d2v ev) {
+        double *lx = op6_lds + slot * (FORM ? 2 : 1) * field, *le = lx + field;
+        if (t.own) *(d2v *)(lx + t.own_l) = xv;
+        if (t.halo) *(d2v *)(lx + t.halo_l) = hx;
+        if constexpr (FORM) {
+            if (t.own) *(d2v *)(le + t.own_l) = ev;
+            if (t.halo) *(d2v *)(le + t.halo_l) = he;
+        }
+    };
+    auto coefs = [&](int k) {
+        if constexpr (!FORM) {
+            const size_t o = zp(k) + t.own_o;
+            eq[0] = ldp<true>(eps + o);
 #pragma unroll
-    for (int d = 0; d < 6; ++d) zload(kfirst - 3 + d, a[d], c[d]);
-    const int lc = (ly + H6) * L6X + lx + H6;
+            for (int d = 0; d < 3; ++d) gq[d] = ldp<true>(G + d * g.N + o);
+        }
+    };
+    halo(kf);
+    stash(0, xq[3], FORM ? eq[FORM ? 3 : 0] : d2v{0, 0});
+    halo(kf + 1);
+    coefs(kf);
+    __syncthreads();
     const double ihx = g.ihx, ihy = g.ihy, ihz = g.ihz, ihx2 = g.ihx2, ihy2 = g.ihy2, ihz2 = g.ihz2;
-    for (int q = q0; q < q1; ++q) {
-        const int k = kb + q;
-        zload(k + 3, a[6], c[6]);
-        const size_t zp = zplane(k);
-        __syncthreads();  // the previous plane's LDS reads are done
+    const int ls = t.ls;
+    for (int q = t.q0; q < t.q1; ++q) {
+        const int k = kb + q, slot = (q - t.q0) & 1;
+        const size_t o = zp(k) + t.own_o;
+        d2v xn = xq[6], en = eq[FORM ? 6 : 0], bv{0, 0};
+        const d2v ec = eq[FORM ? 3 : 0], g0 = gq[0], g1 = gq[FORM ? 0 : 1], g2 = gq[FORM ? 0 : 2];
+        if (MODE != 0) bv = ldp<AL>(b + o);
+        if (q + 1 < t.q1) {
+            stash(slot ^ 1, xq[4], eq[FORM ? 4 : 0]);
+            const size_t on = zp(k + 4) + t.own_o;
+            xn = ldp<AL>(x + on);
+            if constexpr (FORM) en = ldp<true>(eps + on);
+            halo(k + 2);
+            coefs(k + 1);
+        }
+        if (t.own) {
+            const double *lx = op6_lds + slot * (FORM ? 2 : 1) * field + t.own_l, *le = lx + field;
+            const Row8 fx = row8(lx, xq[3]);
+            Row8 fe;
+            d2v xy[6], ey[6];  // rows -3 .. -1, 1 .. 3
+            if constexpr (FORM) fe = row8(le, ec);
 #pragma unroll
-        for (int m = 0; m < T6L; ++m) {
-            const int t = tid + T6N * m;
-            if (t < L6N) {
-                const size_t o = zp + lo[m];
-                if (TRANS) {
-                    const double y = (double)x[o];
-                    s0[t] = (double)eps[o] * y;
-                    s1[t] = (double)Gx[o] * y;
-                    s2[t] = (double)Gy[o] * y;
-                } else {
-                    s0[t] = (double)x[o];
+            for (int n = 0; n < 3; ++n) {
+                xy[n] = *(const d2v *)(lx + (n - 3) * ls);
+                xy[n + 3] = *(const d2v *)(lx + (n + 1) * ls);
+                if constexpr (FORM) {
+                    ey[n] = *(const d2v *)(le + (n - 3) * ls);
+                    ey[n + 3] = *(const d2v *)(le + (n + 1) * ls);
                 }
             }
-        }
-        __syncthreads();
-        if (own) {
-            const size_t o = zp + cc;
-            double v;
-            if (!TRANS) {
-                const double d1x = ihx * (A1 * (s0[lc + 1] - s0[lc - 1]) + A2 * (s0[lc + 2] - s0[lc - 2]) +
-                                          A3 * (s0[lc + 3] - s0[lc - 3]));
-                const double d1y = ihy * (A1 * (s0[lc + L6X] - s0[lc - L6X]) + A2 * (s0[lc + 2 * L6X] - s0[lc - 2 * L6X]) +
-                                          A3 * (s0[lc + 3 * L6X] - s0[lc - 3 * L6X]));
-                const double d1z = ihz * (A1 * (a[4] - a[2]) + A2 * (a[5] - a[1]) + A3 * (a[6] - a[0]));
-                const double xc = a[3];
-                const double d2 = ihx2 * (B0 * xc + B1 * (s0[lc + 1] + s0[lc - 1]) + B2 * (s0[lc + 2] + s0[lc - 2]) +
-                                          B3 * (s0[lc + 3] + s0[lc - 3])) +
-                                  ihy2 * (B0 * xc + B1 * (s0[lc + L6X] + s0[lc - L6X]) +
-                                          B2 * (s0[lc + 2 * L6X] + s0[lc - 2 * L6X]) +
-                                          B3 * (s0[lc + 3 * L6X] + s0[lc - 3 * L6X])) +
-                                  ihz2 * (B0 * xc + B1 * (a[4] + a[2]) + B2 * (a[5] + a[1]) + B3 * (a[6] + a[0]));
-                v = (double)Gx[o] * d1x + (double)Gy[o] * d1y + (double)Gz[o] * d1z + (double)eps[o] * d2;
-            } else {
-                const double d1x = ihx * (A1 * (s1[lc + 1] - s1[lc - 1]) + A2 * (s1[lc + 2] - s1[lc - 2]) +
-                                          A3 * (s1[lc + 3] - s1[lc - 3]));
-                const double d1y = ihy * (A1 * (s2[lc + L6X] - s2[lc - L6X]) + A2 * (s2[lc + 2 * L6X] - s2[lc - 2 * L6X]) +
-                                          A3 * (s2[lc + 3 * L6X] - s2[lc - 3 * L6X]));
-                const double d1z = ihz * (A1 * (c[4] - c[2]) + A2 * (c[5] - c[1]) + A3 * (c[6] - c[0]));
-                const double pc = a[3];
-                const double d2 = ihx2 * (B0 * pc + B1 * (s0[lc + 1] + s0[lc - 1]) + B2 * (s0[lc + 2] + s0[lc - 2]) +
-                                          B3 * (s0[lc + 3] + s0[lc - 3])) +
-                                  ihy2 * (B0 * pc + B1 * (s0[lc + L6X] + s0[lc - L6X]) +
-                                          B2 * (s0[lc + 2 * L6X] + s0[lc - 2 * L6X]) +
-                                          B3 * (s0[lc + 3 * L6X] + s0[lc - 3 * L6X])) +
-                                  ihz2 * (B0 * pc + B1 * (a[4] + a[2]) + B2 * (a[5] + a[1]) + B3 * (a[6] + a[0]));
-                v = -(d1x + d1y + d1z) + d2;
+            d2v v;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const double *f = fx.f + e;
+                double Gx, Gy, Gz;
+                if constexpr (FORM) {
+                    const double *h = fe.f + e;
+                    Gx = d1v(ihx, h[0], h[1], h[2], h[4], h[5], h[6]);
+                    Gy = d1v(ihy, ey[0][e], ey[1][e], ey[2][e], ey[3][e], ey[4][e], ey[5][e]);
+                    Gz = d1v(ihz, eq[0][e], eq[1][e], eq[2][e], eq[4][e], eq[5][e], eq[6][e]);
+                } else {
+                    Gx = g0[e];
+                    Gy = g1[e];
+                    Gz = g2[e];
+                }
+                const double xc = xq[3][e];
+                const double d2 = ihx2 * d2s(f[0], f[1], f[2], xc, f[4], f[5], f[6]) +
+                                  ihy2 * d2s(xy[0][e], xy[1][e], xy[2][e], xc, xy[3][e], xy[4][e], xy[5][e]) +
+                                  ihz2 * d2s(xq[0][e], xq[1][e], xq[2][e], xc, xq[4][e], xq[5][e], xq[6][e]);
+                v[e] = Gx * d1v(ihx, f[0], f[1], f[2], f[4], f[5], f[6]) +
+                       Gy * d1v(ihy, xy[0][e], xy[1][e], xy[2][e], xy[3][e], xy[4][e], xy[5][e]) +
+                       Gz * d1v(ihz, xq[0][e], xq[1][e], xq[2][e], xq[4][e], xq[5][e], xq[6][e]) + ec[e] * d2;
+                if (MODE != 0) v[e] = bv[e] - v[e];
             }
-            if (MODE == 0) out[o] = (T)v;
-            else if (MODE == 1) out[o] = (T)(b[o] - v);
-            else out[(size_t)q * g.plane + cc] = (T)(b[o] - v);
+            stp<AL>(out + (MODE == 2 ? (size_t)q * g.plane + t.own_o : o), v);
         }
 #pragma unroll
-        for (int d = 0; d < 6; ++d) { a[d] = a[d + 1]; c[d] = c[d + 1]; }
+        for (int d = 0; d < 6; ++d) {
+            xq[d] = xq[d + 1];
+            if constexpr (FORM) eq[d] = eq[d + 1];
+        }
+        xq[6] = xn;
+        if constexpr (FORM) eq[6] = en;
+        __syncthreads();
+    }
+}
+
+template <int MODE, class T, class TX, class TE, bool AL>
+__global__ void __launch_bounds__(OP6_NT_TRANS)
+k_op6_trans(Grid6 g, Op6Shape p, const TX *__restrict__ y, const TE *__restrict__ eps, const TE *__restrict__ G,
+            const double *__restrict__ b, T *__restrict__ out) {
+    extern __shared__ __align__(16) double op6_lds[];
+    Op6Pos t;
+    if (!op6_pos(g, p, t)) return;
+    const int field = (p.ty + 2 * H6Y) * t.ls;
+    const int kb = MODE == 2 ? p.k_w0 : 0;
+    const TE *Gx = G, *Gy = G + g.N, *Gz = G + 2 * g.N;
+    auto zp = [&](int k) { return (size_t)wrap(k >= g.nz ? k - g.nz : k, g.nz) * g.plane; };
+    // pq, zq: eps y and Gz y at planes k - 3 .. k + 3; yq: y at planes k + 1 .. k + 3;
+    // ax, ay: Gx and Gy of plane k + 1; h0, h1: the halo pair's eps y and its G y
+    d2v pq[7], zq[7], yq[3], ax, ay, hy{0, 0}, he{0, 0}, hg{0, 0};
+    const int kf = kb + t.q0;
+    d2v y0{0, 0};
+#pragma unroll
+    for (int d = 0; d < 7; ++d) {
+        const size_t o = zp(kf - 3 + d) + t.own_o;
+        const d2v yv = ldp<AL>(y + o);
+        pq[d] = ldp<true>(eps + o) * yv;
+        zq[d] = ldp<true>(Gz + o) * yv;
+        if (d == 3) y0 = yv;
+        if (d > 3) yq[d - 4] = yv;
+    }
+    auto halo = [&](int k) {
+        if (t.halo) {
+            const size_t o = zp(k) + t.halo_o;
+            hy = ldp<AL>(y + o);
+            he = ldp<true>(eps + o);
+            hg = ldp<true>((t.ylo ? Gy : Gx) + o);
+        }
+    };
+    auto grads = [&](int k) {
+        const size_t o = zp(k) + t.own_o;
+        ax = ldp<true>(Gx + o);
+        ay = ldp<true>(Gy + o);
+    };
+    auto stash = [&](int slot, d2v pv, d2v yv) {
+        double *l0 = op6_lds + slot * 3 * field, *l1 = l0 + field, *l2 = l1 + field;
+        if (t.own) {
+            *(d2v *)(l0 + t.own_l) = pv;
+            *(d2v *)(l1 + t.own_l) = ax * yv;
+            *(d2v *)(l2 + t.own_l) = ay * yv;
+        }
+        if (t.halo) {
+            *(d2v *)(l0 + t.halo_l) = he * hy;
+            *(d2v *)((t.ylo ? l2 : l1) + t.halo_l) = hg * hy;
+        }
+    };
+    halo(kf);
+    grads(kf);
+    stash(0, pq[3], y0);
+    halo(kf + 1);
+    grads(kf + 1);
+    __syncthreads();
+    const double ihx = g.ihx, ihy = g.ihy, ihz = g.ihz, ihx2 = g.ihx2, ihy2 = g.ihy2, ihz2 = g.ihz2;
+    const int ls = t.ls;
+    for (int q = t.q0; q < t.q1; ++q) {
+        const int k = kb + q, slot = (q - t.q0) & 1;
+        const size_t o = zp(k) + t.own_o;
+        d2v yn{0, 0}, en{0, 0}, zn{0, 0}, bv{0, 0};
+        if (MODE != 0) bv = ldp<AL>(b + o);
+        if (q + 1 < t.q1) {
+            stash(slot ^ 1, pq[4], yq[0]);
+            const size_t on = zp(k + 4) + t.own_o;
+            yn = ldp<AL>(y + on);
+            en = ldp<true>(eps + on);
+            zn = ldp<true>(Gz + on);
+            halo(k + 2);
+            grads(k + 2);
+        }
+        if (t.own) {
+            const double *l0 = op6_lds + slot * 3 * field + t.own_l, *l1 = l0 + field, *l2 = l1 + field;
+            const Row8 f0 = row8(l0, pq[3]);
+            // the middle pair of Gx y is not needed by the even stencil's own point,
+            // but is by its neighbour's
+            const Row8 f1 = row8(l1, *(const d2v *)l1);
+            d2v p0[6], p2[6];  // rows -3 .. -1, 1 .. 3 of eps y and Gy y
+#pragma unroll
+            for (int n = 0; n < 3; ++n) {
+                p0[n] = *(const d2v *)(l0 + (n - 3) * ls);
+                p0[n + 3] = *(const d2v *)(l0 + (n + 1) * ls);
+                p2[n] = *(const d2v *)(l2 + (n - 3) * ls);
+                p2[n + 3] = *(const d2v *)(l2 + (n + 1) * ls);
+            }
+            d2v v;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const double *f = f0.f + e, *h = f1.f + e;
+                const double pc = pq[3][e];
+                const double d1x = d1v(ihx, h[0], h[1], h[2], h[4], h[5], h[6]);
+                const double d1y = d1v(ihy, p2[0][e], p2[1][e], p2[2][e], p2[3][e], p2[4][e], p2[5][e]);
+                const double d1z = d1v(ihz, zq[0][e], zq[1][e], zq[2][e], zq[4][e], zq[5][e], zq[6][e]);
+                const double d2 = ihx2 * d2s(f[0], f[1], f[2], pc, f[4], f[5], f[6]) +
+                                  ihy2 * d2s(p0[0][e], p0[1][e], p0[2][e], pc, p0[3][e], p0[4][e], p0[5][e]) +
+                                  ihz2 * d2s(pq[0][e], pq[1][e], pq[2][e], pc, pq[4][e], pq[5][e], pq[6][e]);
+                v[e] = -(d1x + d1y + d1z) + d2;
+                if (MODE != 0) v[e] = bv[e] - v[e];
+            }
+            stp<AL>(out + (MODE == 2 ? (size_t)q * g.plane + t.own_o : o), v);
+        }
+#pragma unroll
+        for (int d = 0; d < 6; ++d) { pq[d] = pq[d + 1]; zq[d] = zq[d + 1]; }
+        pq[6] = en * yn;
+        zq[6] = zn * yn;
+        yq[0] = yq[1];
+        yq[1] = yq[2];
+        yq[2] = yn;
+        __syncthreads();
     }
 }
 
@@ -344,37 +563,116 @@ void launch_d1eps(hipStream_t s, const Plan &p, const double *eps, double *G) {
     DWP_LAUNCH_CHECK();
 }
 
-template <int MODE, bool TRANS, class T, class TX = double, class TE = double>
-static void launch_op6_tile(hipStream_t s, const Plan &p, int k_w0, int nplanes, const TX *x, const TE *eps,
-                            const TE *G, const double *b, T *out) {
-    const Grid6 g = make_grid6(p);
-    const int tx = (p.nx + T6X - 1) / T6X, ty = (p.ny + T6Y - 1) / T6Y, tz = (nplanes + Z6 - 1) / Z6;
-    k_op6_tile<MODE, TRANS, T, TX, TE><<<tx * ty * tz, T6N, 0, s>>>(g, k_w0, nplanes, tx, ty, x, eps, G, b, out);
+// Resident blocks of a kernel on the whole device at a block shape, cached per
+// device (a query is a host call per launch otherwise).
+static int op6_slots(const void *fn, int nt, size_t bytes) {
+    struct Key { const void *fn; int dev, nt; size_t bytes; int slots; };
+    static std::vector<Key> cache;
+    static std::mutex mu;
+    std::lock_guard<std::mutex> lock(mu);
+    int dev = 0;
+    DWP_HIP(hipGetDevice(&dev));
+    bool seen = false;
+    for (const Key &k : cache) {
+        if (k.fn != fn || k.dev != dev) continue;
+        seen = true;
+        if (k.nt == nt && k.bytes == bytes) return k.slots;
+    }
+    if (!seen) DWP_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+    int cus = 0, per = 0;
+    DWP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    DWP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, nt, bytes));
+    const int slots = std::max(1, cus * per);
+    if (cache.size() < 256) cache.push_back(Key{fn, dev, nt, bytes, slots});
+    return slots;
+}
+
+// Tile and chunk of the operator: the widest tile row of whole pairs up to 48
+// that divides nx (48 pairs of 96 points, 32 of a power of two), as many rows
+// as divide ny within the kernel's threads (32 at most), and the chunk length
+// whose blocks fill whole rounds of the resident ones (a chunk costs its planes
+// and about five steps to fill its registers).  Tall tiles save halo work:
+// A6 at 192 x 192 x 384 takes 173 us with 4 rows of 48 pairs, 121 with 8, 86
+// with 16; 88 with 24 rows of 32 pairs, 91 with 32 rows of 24.  The transpose,
+// whose registers allow 512 threads, is fastest at 8 rows of 48 (768 threads
+// spill: 2 % more on the 128 x 128 x 256 step).
+static Op6Shape op6_shape(const Plan &p, int k_w0, int nplanes, const void *fn, int most, int fields, int &nt,
+                          size_t &bytes) {
+    Op6Shape s{};
+    s.k_w0 = k_w0;
+    s.nplanes = nplanes;
+    for (int w = 1; w <= 48 && w <= p.nx / 2; ++w)
+        if (p.nx / 2 % w == 0) s.wp = w;
+    for (int t = 1; t <= 32 && t * s.wp <= most; ++t)
+        if (p.ny % t == 0) s.ty = t;
+    s.tiles_x = p.nx / 2 / s.wp;
+    s.tiles_y = p.ny / s.ty;
+    const int nh = 4 * s.ty + 2 * H6Y * s.wp;  // halo pairs, one per thread
+    nt = (std::max(s.wp * s.ty, nh) + 63) / 64 * 64;
+    bytes = sizeof(double) * 2 * fields * (size_t)(s.ty + 2 * H6Y) * (2 * s.wp + 2 * H6X);
+    const long slots = (long)op6_slots(fn, nt, bytes);
+    const long tiles = (long)s.tiles_x * s.tiles_y;
+    long best = -1;
+    for (int c = 1; c <= 64; ++c) {
+        const long blocks = tiles * ((nplanes + c - 1) / c), cost = (blocks + slots - 1) / slots * (c + 5);
+        if (best < 0 || cost < best) { best = cost; s.kc = c; }
+    }
+    s.nb = (int)(tiles * ((nplanes + s.kc - 1) / s.kc));
+    return s;
+}
+
+static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+template <int MODE, class T, class TX, class TE, bool AL>
+static void op6_fwd(hipStream_t s, const Plan &p, int k_w0, int nplanes, const TX *x, const TE *eps, const TE *G,
+                    const double *b, T *out) {
+    int nt = 0;
+    size_t bytes = 0;
+    const Op6Shape sh = op6_shape(p, k_w0, nplanes, reinterpret_cast<const void *>(&k_op6_fwd<MODE, T, TX, TE, AL>),
+                                  OP6_NT_FWD, sizeof(TE) == 8 ? 2 : 1, nt, bytes);
+    k_op6_fwd<MODE, T, TX, TE, AL><<<(sh.nb + 7) / 8 * 8, nt, bytes, s>>>(make_grid6(p), sh, x, eps, G, b, out);
     DWP_LAUNCH_CHECK();
+}
+template <int MODE, class T, class TX, class TE, bool AL>
+static void op6_trans(hipStream_t s, const Plan &p, int k_w0, int nplanes, const TX *y, const TE *eps, const TE *G,
+                      const double *b, T *out) {
+    int nt = 0;
+    size_t bytes = 0;
+    const Op6Shape sh = op6_shape(p, k_w0, nplanes, reinterpret_cast<const void *>(&k_op6_trans<MODE, T, TX, TE, AL>),
+                                  OP6_NT_TRANS, 3, nt, bytes);
+    k_op6_trans<MODE, T, TX, TE, AL><<<(sh.nb + 7) / 8 * 8, nt, bytes, s>>>(make_grid6(p), sh, y, eps, G, b, out);
+    DWP_LAUNCH_CHECK();
+}
+// the caller's arrays (x, b, out) may be aligned to 8 bytes only
+template <int MODE, class T>
+static void op6_any(hipStream_t s, const Plan &p, int k_w0, int nplanes, const double *x, const double *eps,
+                    const double *G, const double *b, T *out, bool trans) {
+    const bool al = aligned16(x) && aligned16(out) && (MODE == 0 || aligned16(b));
+    if (trans) {
+        if (al) op6_trans<MODE, T, double, double, true>(s, p, k_w0, nplanes, x, eps, G, b, out);
+        else op6_trans<MODE, T, double, double, false>(s, p, k_w0, nplanes, x, eps, G, b, out);
+    } else {
+        if (al) op6_fwd<MODE, T, double, double, true>(s, p, k_w0, nplanes, x, eps, nullptr, b, out);
+        else op6_fwd<MODE, T, double, double, false>(s, p, k_w0, nplanes, x, eps, nullptr, b, out);
+    }
 }
 
 void launch_apply6_f32(hipStream_t s, const Plan &p, const float *x, const float *eps, const float *G, float *out,
                        bool trans) {
-    if (trans) launch_op6_tile<0, true, float, float, float>(s, p, 0, p.nz, x, eps, G, nullptr, out);
-    else launch_op6_tile<0, false, float, float, float>(s, p, 0, p.nz, x, eps, G, nullptr, out);
+    if (trans) op6_trans<0, float, float, float, true>(s, p, 0, p.nz, x, eps, G, nullptr, out);
+    else op6_fwd<0, float, float, float, true>(s, p, 0, p.nz, x, eps, G, nullptr, out);
 }
 
 void launch_apply6(hipStream_t s, const Plan &p, const double *x, const double *eps, const double *G,
                    const double *b, double *out, bool residual, bool trans) {
-    if (residual) {
-        if (trans) launch_op6_tile<1, true, double>(s, p, 0, p.nz, x, eps, G, b, out);
-        else launch_op6_tile<1, false, double>(s, p, 0, p.nz, x, eps, G, b, out);
-    } else {
-        if (trans) launch_op6_tile<0, true, double>(s, p, 0, p.nz, x, eps, G, b, out);
-        else launch_op6_tile<0, false, double>(s, p, 0, p.nz, x, eps, G, b, out);
-    }
+    if (residual) op6_any<1>(s, p, 0, p.nz, x, eps, G, b, out, trans);
+    else op6_any<0>(s, p, 0, p.nz, x, eps, G, b, out, trans);
 }
 
 template <class T>
 void launch_wet_residual6(hipStream_t s, const Plan &p, const double *v, const double *dD, const double *eps,
                           const double *G, T *fW, bool trans) {
-    if (trans) launch_op6_tile<2, true, T>(s, p, p.k_w0, p.nw, dD, eps, G, v, fW);
-    else launch_op6_tile<2, false, T>(s, p, p.k_w0, p.nw, dD, eps, G, v, fW);
+    op6_any<2>(s, p, p.k_w0, p.nw, dD, eps, G, v, fW, trans);
 }
 template <class T>
 void launch_wet6(hipStream_t s, const Plan &p, const Level &L, const T *u, T *out, const double *eps, const double *G,

@@ -56,6 +56,49 @@ def test_apply_matches_oracle(torch, n):
     s.close()
 
 
+# tiles of 4, 9, 27, 32 and 48 pairs, of 8 to 32 rows, one or several along x
+# and y; chunks that do and do not divide nz
+@pytest.mark.parametrize("n", [(8, 96, 18), (18, 54, 24), (54, 16, 8), (96, 64, 12), (128, 32, 72), (192, 8, 162)])
+def test_apply_on_tile_edges_and_arrays_off_16_bytes(torch, n):
+    L = (0.3 * n[0], 0.25 * n[1], 0.2 * n[2])
+    eps, _ = W.random_fields(n, 33, eps_lo=1.0, eps_hi=20.0)
+    phi = np.random.default_rng(3).normal(size=eps.shape)
+    s = _solver(n, L, z_wet_lo=0.2 * L[2], z_wet_hi=0.9 * L[2])
+    s.set_epsilon(_dev(torch, eps))
+    ref = S.apply_A6(phi, eps, s.h)
+    x = _dev(torch, phi)
+    out = s.apply_operator(x).cpu().numpy()
+    assert np.abs(out - ref).max() <= 1e-13 * np.abs(ref).max()
+    off = torch.empty(x.numel() + 1, dtype=torch.float64, device="cuda")[1:].view(x.shape)
+    assert off.data_ptr() % 16 == 8
+    off.copy_(x)
+    assert np.array_equal(s.apply_operator(off).cpu().numpy(), out)
+    assert np.array_equal(s.apply_operator(x, out=off).cpu().numpy(), out)
+    s.close()
+
+
+@pytest.mark.parametrize("n", [(18, 8, 54), (54, 12, 16), (8, 36, 24)])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_adjoint_on_tile_edges(torch, n, precision):
+    """dE/d eps through the transposed operator where its tiles are narrow, low or
+    split, with a permittivity these grids resolve."""
+    L = (0.3 * n[0], 0.25 * n[1], 0.2 * n[2])
+    z, y, x = np.indices((n[2], n[1], n[0]))
+    eps = 3.0 + np.cos(2 * np.pi * x / n[0]) * np.cos(2 * np.pi * y / n[1]) + 0.5 * np.sin(2 * np.pi * z / n[2])
+    rho = np.random.default_rng(4).normal(size=eps.shape)
+    rho -= rho.mean()
+    tol = 1e-11 if precision == 0 else 1e-9
+    s = _solver(n, L, z_wet_lo=0.3 * L[2], z_wet_hi=0.9 * L[2], tol=tol, precision=precision, cycles=0,
+                krylov_fp32=precision, fft_fp32=precision)
+    s.set_epsilon(_dev(torch, eps))
+    s.solve(_dev(torch, rho))
+    g = s.eps_gradient().cpu().numpy()
+    phi = S.solve6(rho, eps, s.h, tol=1e-13)
+    ref = S.eps_gradient6(phi, S.adjoint6(rho, eps, s.h, tol=1e-13), s.h)
+    assert np.abs(g - ref).max() <= 1e4 * tol * np.abs(ref).max()
+    s.close()
+
+
 @pytest.mark.parametrize("n", [(24, 36, 48), (16, 8, 96)])
 def test_vacuum_solve_uses_the_sixth_order_symbol(torch, n):
     L = (6.0, 9.0, 12.0)
