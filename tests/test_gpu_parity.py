@@ -377,6 +377,23 @@ def test_float32_vacuum_solve_matches_oracle(torch, n):
     assert _rel(out, ref) <= 2e-5
 
 
+# rows of 4 m and 4 m + 2 values, an odd and an even number of spectrum pairs, and a
+# last block of lines that is not full
+@pytest.mark.parametrize("fp32", [0, 1])
+@pytest.mark.parametrize("n", [(18, 16, 24), (24, 18, 16), (54, 36, 18), (162, 8, 12), (96, 54, 24), (8, 8, 54)])
+def test_scaled_dry_update_matches_oracle(torch, n, fp32):
+    """s L^-1 (s r), s = eps^-1/2: the split without a wet correction."""
+    L = (0.2 * n[0], 0.3 * n[1], 0.1 * n[2])
+    eps, r = W.random_fields(n, 23)
+    s = _solver(torch, n, L, z_wet_lo=0.3 * L[2], z_wet_hi=L[2], precision=fp32, fft_fp32=fp32, cycles=0, scaled_dry=1)
+    s.set_epsilon(_dev(torch, eps))
+    out = _host(s.apply_split(_dev(torch, r)))
+    si = 1.0 / np.sqrt(eps)
+    ref = si * O.vacuum_solve(si * r, s.h)
+    # the bars of the unscaled solves
+    assert _rel(out, ref) <= (2e-5 if fp32 else 1e-12)
+
+
 @pytest.mark.parametrize("fp32", [0, 1])
 @pytest.mark.parametrize("n", [(4096, 8, 8), (8, 4096, 8), (8, 8, 4096)])
 def test_vacuum_solve_at_the_longest_axis(torch, n, fp32):
