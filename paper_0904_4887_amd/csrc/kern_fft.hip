@@ -12,6 +12,7 @@
 //   z  : forward along z, multiply by -1/(N lambda), inverse along z
 //   y  : inverse
 //   x  : inverse of two rows at once (C2R)
+// or three where a whole z plane fits a block (x and y, z, y and x).
 // Each 1-D transform is a Stockham autosort FFT with radix-8, -6, -4, -3 and -2
 // stages; a stage reads its inputs into registers, synchronises, and writes
 // its outputs back in place.  The spectrum and the transforms run in float64,
@@ -162,7 +163,26 @@ template <class C> struct DFT<8, C> {
     }
 };
 
-// One Stockham stage of radix R on B = 2^lb lines of length n held in LDS;
+// The lines of a block, B = 2^lb of them or any number: work item w is
+// butterfly i of line l with w = i B + l.
+struct Pow2Lines {
+    int lb;
+    __device__ __forceinline__ int times(int i) const { return i << lb; }
+    __device__ __forceinline__ void split(int w, int &l, int &i) const {
+        l = w & ((1 << lb) - 1);
+        i = w >> lb;
+    }
+};
+struct AnyLines {
+    Div d;
+    __device__ __forceinline__ int times(int i) const { return i * d.d; }
+    __device__ __forceinline__ void split(int w, int &l, int &i) const {
+        i = udiv(w, d);
+        l = w - i * d.d;
+    }
+};
+
+// One Stockham stage of radix R on the B lines ln of length n held in LDS;
 // element t of line l sits at buf[l * ls + t * es].  p = product of the
 // radices of the earlier stages.  Butterfly i of a line reads
 // x_q = buf[i + q n/R], twiddles x_q by exp(-+2 pi i q (i mod p) / (p R)),
@@ -170,22 +190,23 @@ template <class C> struct DFT<8, C> {
 // IL: the lines are interleaved (es = B, ls = 1: element t of line l at
 // t B + l), so that work item w = i B + l reads x_q at w + q T B and writes
 // output r at ((i - k) R + k) B + l + r p B without per-element multiplies.
-template <int R, class C, int MAXE, int NT, bool IL>
-__device__ void stage(C *buf, int n, int p, unsigned pm, int tstride, int lb, int es, int ls,
+template <int R, class C, int MAXE, int NT, bool IL, class LN>
+__device__ void stage(C *buf, int n, int p, unsigned pm, int tstride, LN ln, int es, int ls,
                       const C *__restrict__ tw, bool inv) {
-    // a block whose plan holds a radix-6 stage has at most 6 NT values (the
-    // host's tile budget), so that the radix-6 stage is one butterfly per thread
-    constexpr int E = R == 6 && MAXE > 6 * NT ? 6 * NT : MAXE;
+    // a block of 2^lb lines whose plan holds a radix-6 stage has at most 6 NT
+    // values (the host's tile budget), so that the radix-6 stage is one
+    // butterfly per thread
+    constexpr int E = R == 6 && std::is_same_v<LN, Pow2Lines> && MAXE > 6 * NT ? 6 * NT : MAXE;
     constexpr int K = (E / R + NT - 1) / NT;
     const int T = n / R;
-    const int items = T << lb;
-    const int bmask = (1 << lb) - 1;
+    const int items = ln.times(T);
     C x[K][R];
 #pragma unroll
     for (int m = 0; m < K; ++m) {
         const int w = threadIdx.x + m * NT;
         if (w < items) {
-            const int l = w & bmask, i = w >> lb;
+            int l, i;
+            ln.split(w, l, i);
 #pragma unroll
             for (int q = 0; q < R; ++q) x[m][q] = IL ? buf[w + q * items] : buf[l * ls + (i + q * T) * es];
         }
@@ -195,7 +216,8 @@ __device__ void stage(C *buf, int n, int p, unsigned pm, int tstride, int lb, in
     for (int m = 0; m < K; ++m) {
         const int w = threadIdx.x + m * NT;
         if (w < items) {
-            const int l = w & bmask, i = w >> lb;
+            int l, i;
+            ln.split(w, l, i);
             const int k = p > 1 ? i - p * (int)__umulhi((unsigned)i, pm) : 0;
             if (p > 1) {
                 const int kt = k * tstride;
@@ -208,7 +230,7 @@ __device__ void stage(C *buf, int n, int p, unsigned pm, int tstride, int lb, in
             }
             DFT<R, C>::run(x[m], inv);
             const int j = (i - k) * R + k;
-            const int jb = (j << lb) + l, pb = p << lb;
+            const int jb = ln.times(j) + l, pb = ln.times(p);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (IL) buf[jb + r * pb] = x[m][r];
@@ -221,16 +243,20 @@ __device__ void stage(C *buf, int n, int p, unsigned pm, int tstride, int lb, in
 
 // R6: the plan may hold a radix-6 stage (a kernel built without it keeps the
 // registers the radix-6 stage would need)
-template <bool R6, bool IL, class C, int MAXE = FFT_MAXE, int NT = FFT_THREADS>
-__device__ void fft_lines(C *buf, const Radices &rd, int lb, int es, int ls, const C *__restrict__ tw, bool inv) {
+template <bool R6, bool IL, class C, int MAXE, int NT, class LN>
+__device__ void fft_lines_of(C *buf, const Radices &rd, LN ln, int es, int ls, const C *__restrict__ tw, bool inv) {
     for (int s = 0; s < rd.nst; ++s) {
         const int R = rd.r[s];
-        if (R == 8) stage<8, C, MAXE, NT, IL>(buf, rd.n, rd.p[s], rd.pm[s], rd.tstride[s], lb, es, ls, tw, inv);
-        else if (R6 && R == 6) stage<6, C, MAXE, NT, IL>(buf, rd.n, rd.p[s], rd.pm[s], rd.tstride[s], lb, es, ls, tw, inv);
-        else if (R == 4) stage<4, C, MAXE, NT, IL>(buf, rd.n, rd.p[s], rd.pm[s], rd.tstride[s], lb, es, ls, tw, inv);
-        else if (R == 3) stage<3, C, MAXE, NT, IL>(buf, rd.n, rd.p[s], rd.pm[s], rd.tstride[s], lb, es, ls, tw, inv);
-        else stage<2, C, MAXE, NT, IL>(buf, rd.n, rd.p[s], rd.pm[s], rd.tstride[s], lb, es, ls, tw, inv);
+        if (R == 8) stage<8, C, MAXE, NT, IL>(buf, rd.n, rd.p[s], rd.pm[s], rd.tstride[s], ln, es, ls, tw, inv);
+        else if (R6 && R == 6) stage<6, C, MAXE, NT, IL>(buf, rd.n, rd.p[s], rd.pm[s], rd.tstride[s], ln, es, ls, tw, inv);
+        else if (R == 4) stage<4, C, MAXE, NT, IL>(buf, rd.n, rd.p[s], rd.pm[s], rd.tstride[s], ln, es, ls, tw, inv);
+        else if (R == 3) stage<3, C, MAXE, NT, IL>(buf, rd.n, rd.p[s], rd.pm[s], rd.tstride[s], ln, es, ls, tw, inv);
+        else stage<2, C, MAXE, NT, IL>(buf, rd.n, rd.p[s], rd.pm[s], rd.tstride[s], ln, es, ls, tw, inv);
     }
+}
+template <bool R6, bool IL, class C, int MAXE = FFT_MAXE, int NT = FFT_THREADS>
+__device__ void fft_lines(C *buf, const Radices &rd, int lb, int es, int ls, const C *__restrict__ tw, bool inv) {
+    fft_lines_of<R6, IL, C, MAXE, NT>(buf, rd, Pow2Lines{lb}, es, ls, tw, inv);
 }
 
 // A block's loads of n_el values from global memory: KL per thread issued
@@ -551,6 +577,178 @@ k_fft_y(cplx<S> *__restrict__ c, Radices rd, const cplx<S> *__restrict__ tw, int
     }
 }
 
+// ---------------------------------------------------------------- x and y passes of a small plane
+// One block of NT threads transforms a whole z plane along x and along y, so
+// the half spectrum does not go to memory in between: the ny / 2 packed lines
+// of the x pass (padded to n + 1), split in registers into the ny x nkx values
+// of the y pass (interleaved: value (y, k) at y nkx + k) in the same LDS.  The
+// arithmetic is that of the separate passes.  At most PE NT values of either
+// form (PE per thread; what a stage keeps in registers).  Bound by the LDS
+// traffic and the barriers of a block's own chain of stages, the memory idle
+// meanwhile; the separate passes overlap their blocks but move the spectrum
+// four more times.  Whole solve, five passes against three, us: 27 -> 19.5 at
+// 32 x 32 x 64, 70 -> 51 at 96 x 96 x 192, 106 -> 84 at 128 x 128 x 256 in
+// float64; 51.5 -> 40, 74 -> 55 in float32.  (Planes of up to 192 x 192 in
+// float32, 20 values a thread: 157 -> 187 us at 192 x 192 x 384, one block a
+// CU and nothing to overlap with.)
+template <class S, class TI, bool SC, int NT, int PE>
+__global__ void __launch_bounds__(NT)
+k_fft_xy_fwd(const TI *__restrict__ in, const double *__restrict__ sinv, cplx<S> *__restrict__ out, Radices rx,
+             Radices ry, const cplx<S> *__restrict__ twx, const cplx<S> *__restrict__ twy, int ldc, Div dl, Div dw,
+             Div dk) {
+    using C = cplx<S>;
+    constexpr int MAXE = PE * NT;
+    typedef TI TIW __attribute__((ext_vector_type(2)));
+    typedef double DW __attribute__((ext_vector_type(2)));
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    C *lds = reinterpret_cast<C *>(lds_raw);
+    const int n = rx.n, ls = n + 1, ny = ry.n, nl = ny >> 1, nkx = dk.d;
+    const size_t z = blockIdx.x;
+    C *tx = lds + max(nl * ls, ny * nkx), *ty = tx + n;
+    for (int e = threadIdx.x; e < n + ny; e += NT) tx[e] = e < n ? twx[e] : twy[e - n];
+    {
+        const int nw = n >> 1;  // dw divides by it
+        constexpr int KV = (PE + 1) / 2;
+        TIW va[KV], vb[KV];
+        DW sa[SC ? KV : 1], sb[SC ? KV : 1];
+#pragma unroll
+        for (int m = 0; m < KV; ++m) {
+            const int e = threadIdx.x + m * NT;
+            if (e < nl * nw) {
+                const int l = udiv(e, dw), t = e - l * nw;
+                const size_t ia = (z * ny + 2 * l) * n + 2 * t;
+                va[m] = *reinterpret_cast<const TIW *>(in + ia);
+                vb[m] = *reinterpret_cast<const TIW *>(in + ia + n);
+                if constexpr (SC) {
+                    sa[m] = *reinterpret_cast<const DW *>(sinv + ia);
+                    sb[m] = *reinterpret_cast<const DW *>(sinv + ia + n);
+                }
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < KV; ++m) {
+            const int e = threadIdx.x + m * NT;
+            if (e < nl * nw) {
+                const int l = udiv(e, dw), t = e - l * nw;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    double a = (double)va[m][q], b = (double)vb[m][q];
+                    if constexpr (SC) { a *= sa[m][q]; b *= sb[m][q]; }
+                    lds[l * ls + 2 * t + q] = mk<C>((S)a, (S)b);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    fft_lines_of<true, false, C, MAXE, NT>(lds, rx, AnyLines{dl}, 1, ls, tx, false);
+    {
+        constexpr int KS = (PE + 1) / 2;
+        C A[KS], Bv[KS];
+        const S h = (S)0.5;
+#pragma unroll
+        for (int m = 0; m < KS; ++m) {
+            const int e = threadIdx.x + m * NT;
+            if (e < nl * nkx) {
+                const int l = udiv(e, dk), k = e - l * nkx;
+                const C v = lds[l * ls + k], vc = lds[l * ls + (k == 0 ? 0 : n - k)];
+                A[m] = mk<C>(h * (v.x + vc.x), h * (v.y - vc.y));
+                Bv[m] = mk<C>(h * (v.y + vc.y), -h * (v.x - vc.x));
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < KS; ++m) {
+            const int e = threadIdx.x + m * NT;
+            if (e < nl * nkx) {
+                const int l = udiv(e, dk);
+                lds[e + l * nkx] = A[m];           // (2 l) nkx + k
+                lds[e + (l + 1) * nkx] = Bv[m];
+            }
+        }
+    }
+    __syncthreads();
+    fft_lines_of<true, true, C, MAXE, NT>(lds, ry, AnyLines{dk}, nkx, 1, ty, false);
+    for (int e = threadIdx.x; e < ny * nkx; e += NT) {
+        const int y = udiv(e, dk), k = e - y * nkx;
+        out[(z * ny + y) * ldc + k] = lds[e];
+    }
+}
+
+template <class S, class TO, bool SC, int NT, int PE>
+__global__ void __launch_bounds__(NT)
+k_fft_xy_inv(const cplx<S> *__restrict__ in, const double *__restrict__ sinv, TO *__restrict__ out, Radices rx,
+             Radices ry, const cplx<S> *__restrict__ twx, const cplx<S> *__restrict__ twy, int ldc, Div dl, Div dw,
+             Div dk) {
+    using C = cplx<S>;
+    constexpr int MAXE = PE * NT;
+    typedef TO TOW __attribute__((ext_vector_type(2)));
+    typedef double DW __attribute__((ext_vector_type(2)));
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    C *lds = reinterpret_cast<C *>(lds_raw);
+    const int n = rx.n, ls = n + 1, ny = ry.n, nl = ny >> 1, nkx = dk.d;
+    const size_t z = blockIdx.x;
+    C *tx = lds + max(nl * ls, ny * nkx), *ty = tx + n;
+    for (int e = threadIdx.x; e < n + ny; e += NT) tx[e] = e < n ? twx[e] : twy[e - n];
+    load_batched<6, NT, C>(
+        ny * nkx,
+        [&](int e) {
+            const int y = udiv(e, dk), k = e - y * nkx;
+            return in[(z * ny + y) * ldc + k];
+        },
+        [&](int e, C v) { lds[e] = v; });
+    __syncthreads();
+    fft_lines_of<true, true, C, MAXE, NT>(lds, ry, AnyLines{dk}, nkx, 1, ty, true);
+    {
+        constexpr int KS = (PE + 1) / 2;
+        C A[KS], Bv[KS];
+#pragma unroll
+        for (int m = 0; m < KS; ++m) {
+            const int e = threadIdx.x + m * NT;
+            if (e < nl * nkx) {
+                const int l = udiv(e, dk);
+                A[m] = lds[e + l * nkx];
+                Bv[m] = lds[e + (l + 1) * nkx];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < KS; ++m) {
+            const int e = threadIdx.x + m * NT;
+            if (e < nl * nkx) {
+                const int l = udiv(e, dk), k = e - l * nkx;
+                C a = A[m], b = Bv[m];
+                const bool self = k == 0 || 2 * k == n;
+                if (self) { a.y = 0; b.y = 0; }
+                lds[l * ls + k] = mk<C>(a.x - b.y, a.y + b.x);
+                if (!self) lds[l * ls + n - k] = mk<C>(a.x + b.y, b.x - a.y);
+            }
+        }
+    }
+    __syncthreads();
+    fft_lines_of<true, false, C, MAXE, NT>(lds, rx, AnyLines{dl}, 1, ls, tx, true);
+    const int nw = n >> 1;  // dw divides by it
+    for (int e = threadIdx.x; e < nl * nw; e += NT) {
+        const int l = udiv(e, dw), t = e - l * nw;
+        const size_t ia = (z * ny + 2 * l) * n + 2 * t;
+        const C v0 = lds[l * ls + 2 * t], v1 = lds[l * ls + 2 * t + 1];
+        TOW a, b;
+        if constexpr (SC) {
+            const DW sa = *reinterpret_cast<const DW *>(sinv + ia), sb = *reinterpret_cast<const DW *>(sinv + ia + n);
+            a[0] = (TO)((double)v0.x * sa[0]);
+            a[1] = (TO)((double)v1.x * sa[1]);
+            b[0] = (TO)((double)v0.y * sb[0]);
+            b[1] = (TO)((double)v1.y * sb[1]);
+        } else {
+            a[0] = (TO)v0.x;
+            a[1] = (TO)v1.x;
+            b[0] = (TO)v0.y;
+            b[1] = (TO)v1.y;
+        }
+        *reinterpret_cast<TOW *>(out + ia) = a;
+        *reinterpret_cast<TOW *>(out + ia + n) = b;
+    }
+}
+
 // ---------------------------------------------------------------- z pass + Green
 // -1 / lambda through the hardware reciprocal (two Newton steps in float64).
 __device__ __forceinline__ double neg_recip(double d) {
@@ -663,6 +861,22 @@ int tile_log2(int n, int budget) {
     return lb;
 }
 
+// Whether the x and y passes of a plane of pv values run in one block (bytes
+// of LDS), nz blocks in all.  Small planes always do (8 x 8 x 8: 22 -> 16 us).
+// Larger ones need the planes to occupy the chip: a block's chain of stages
+// takes what it takes however few there are (96 x 96 in float64: 29 us by
+// separate passes and 31 in one at nz = 8, 39 and 37.5 at 64, 70 and 51 at
+// 192).  Past PLANE_MID one block fills a CU, so the last round over the 256
+// CUs has to be worth it (128 x 128: 112 and 114 us at nz = 288, 138 and 127
+// at 384, 182 and 185 at 576; 40 and 48 at 32, 54 and 54 at 64).
+constexpr int PLANE_SMALL = 6 * 512, PLANE_MID = 6 * 1024, PLANE_MAX = 10 * 1024;
+bool plane_pass(int pv, size_t bytes, int nz) {
+    if (pv <= PLANE_SMALL) return true;
+    if (pv <= PLANE_MID) return nz >= 64;
+    const int last = nz % 256;
+    return pv <= PLANE_MAX && bytes <= 160 * 1024 && (last == 0 || last >= 96);
+}
+
 }  // namespace
 
 // Radix plan, twiddles and the discrete symbol 4 sin^2(pi m / n) / h^2 of one
@@ -773,8 +987,32 @@ static void vacuum_solve_t(hipStream_t st, const Plan &p, const FFTAxis &ax, con
             DWP_LAUNCH_CHECK();
         });
     };
+    // both passes of a plane in one block
+    const int pv = std::max(p.ny / 2 * (p.nx + 1), p.ny * p.nkx);
+    const size_t ldsp = sizeof(C) * ((size_t)pv + p.nx + p.ny);
+    const bool plane = plane_pass(pv, ldsp, p.nz);
+    const Div dl = make_div(p.ny / 2), dw2 = make_div(p.nx / 2);
+    auto with_plane = [&](auto &&f) {
+        auto size = [&](auto sc) {
+            using std::integral_constant;
+            if (pv <= PLANE_SMALL) f(sc, integral_constant<int, 512>{}, integral_constant<int, 6>{});
+            else if (pv <= PLANE_MID) f(sc, integral_constant<int, 1024>{}, integral_constant<int, 6>{});
+            else f(sc, integral_constant<int, 1024>{}, integral_constant<int, 10>{});
+        };
+        if (sinv) size(std::true_type{});
+        else size(std::false_type{});
+    };
     ev = pb(PG_FFT_X);
-    with6(has6(ax), [&](auto r6) {
+    if (plane) with_plane([&](auto sc, auto nt, auto pe_) {
+        constexpr bool SC = decltype(sc)::value;
+        constexpr int NT = decltype(nt)::value, PE = decltype(pe_)::value;
+        static std::atomic<unsigned> attr{0};
+        lds_attr(fptr(&k_fft_xy_fwd<S, TI, SC, NT, PE>), attr, ldsp);
+        k_fft_xy_fwd<S, TI, SC, NT, PE><<<p.nz, NT, ldsp, st>>>(r, sinv, cbuf, RD(ax), RD(ay), TW(ax), TW(ay), p.ldc, dl,
+                                                            dw2, dk);
+        DWP_LAUNCH_CHECK();
+    });
+    else with6(has6(ax), [&](auto r6) {
         with_rows([&](auto sc, auto w) {
             constexpr bool R6 = decltype(r6)::value, SC = decltype(sc)::value;
             constexpr int W = decltype(w)::value;
@@ -786,9 +1024,11 @@ static void vacuum_solve_t(hipStream_t st, const Plan &p, const FFTAxis &ax, con
         });
     });
     pe(ev, PG_FFT_X, bx);
-    ev = pb(PG_FFT_Y);
-    y_pass(std::false_type{});
-    pe(ev, PG_FFT_Y, 2.0 * cb * Cn);
+    if (!plane) {
+        ev = pb(PG_FFT_Y);
+        y_pass(std::false_type{});
+        pe(ev, PG_FFT_Y, 2.0 * cb * Cn);
+    }
     // z pass with the Green's function (lines of 8 kx; the twiddles follow
     // the lines in LDS)
     ev = pb(PG_FFT_Z);
@@ -808,11 +1048,22 @@ static void vacuum_solve_t(hipStream_t st, const Plan &p, const FFTAxis &ax, con
         DWP_LAUNCH_CHECK();
     });
     pe(ev, PG_FFT_Z, 2.0 * cb * Cn);
-    ev = pb(PG_FFT_Y);
-    y_pass(std::true_type{});
-    pe(ev, PG_FFT_Y, 2.0 * cb * Cn);
+    if (!plane) {
+        ev = pb(PG_FFT_Y);
+        y_pass(std::true_type{});
+        pe(ev, PG_FFT_Y, 2.0 * cb * Cn);
+    }
     ev = pb(PG_FFT_X);
-    with6(has6(ax), [&](auto r6) {
+    if (plane) with_plane([&](auto sc, auto nt, auto pe_) {
+        constexpr bool SC = decltype(sc)::value;
+        constexpr int NT = decltype(nt)::value, PE = decltype(pe_)::value;
+        static std::atomic<unsigned> attr{0};
+        lds_attr(fptr(&k_fft_xy_inv<S, TO, SC, NT, PE>), attr, ldsp);
+        k_fft_xy_inv<S, TO, SC, NT, PE><<<p.nz, NT, ldsp, st>>>(cbuf, sinv, out, RD(ax), RD(ay), TW(ax), TW(ay), p.ldc, dl,
+                                                            dw2, dk);
+        DWP_LAUNCH_CHECK();
+    });
+    else with6(has6(ax), [&](auto r6) {
         with_rows([&](auto sc, auto w) {
             constexpr bool R6 = decltype(r6)::value, SC = decltype(sc)::value;
             constexpr int W = decltype(w)::value;

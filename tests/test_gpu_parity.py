@@ -394,6 +394,27 @@ def test_scaled_dry_update_matches_oracle(torch, n, fp32):
     assert _rel(out, ref) <= (2e-5 if fp32 else 1e-12)
 
 
+# planes transformed in one block of 512 threads (3024 of at most 3072 values), of 1024
+# (4704 and 5940 of 6144; fewer than 64 planes: separate passes), with up to ten values
+# a thread (9360 and 10240 of 10240, the latter in float32 only: the LDS; fewer than 96
+# planes or a last round of 32: separate passes), and past all of them
+@pytest.mark.parametrize("fp32,scaled", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("n", [(54, 108, 8), (96, 96, 54), (96, 96, 64), (108, 108, 72), (128, 144, 96),
+                               (128, 144, 72), (96, 128, 288), (8, 2048, 96), (162, 144, 96)])
+def test_dry_update_by_planes_matches_oracle(torch, n, fp32, scaled):
+    L = (0.2 * n[0], 0.2 * n[1], 0.2 * n[2])
+    eps, r = W.random_fields(n, 29)
+    s = _solver(torch, n, L, z_wet_lo=0.3 * L[2], z_wet_hi=L[2], precision=fp32, fft_fp32=fp32, cycles=0,
+                scaled_dry=scaled)
+    s.set_epsilon(_dev(torch, eps))
+    out = _host(s.apply_split(_dev(torch, r)))
+    si = 1.0 / np.sqrt(eps) if scaled else 1.0
+    ref = si * O.vacuum_solve(si * r, s.h)
+    # the bars of the other solves; a line of 2048 gains rounding as in the test of 4096
+    long = max(n) / 512 if max(n) > 512 else 1.0
+    assert _rel(out, ref) <= (2e-5 if fp32 else 1e-12) * long**2
+
+
 @pytest.mark.parametrize("fp32", [0, 1])
 @pytest.mark.parametrize("n", [(4096, 8, 8), (8, 4096, 8), (8, 8, 4096)])
 def test_vacuum_solve_at_the_longest_axis(torch, n, fp32):
