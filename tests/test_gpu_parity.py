@@ -87,6 +87,31 @@ def test_build_epsilon_matches_oracle(torch, exclusion):
     assert np.abs(eps - ref).max() <= 1e-12 * 78.36
 
 
+# four nodes a thread on 5166 tiles with remainders along x, y and z, one on 20;
+# atoms past one batch of 256, around the whole cell and partly buried
+@pytest.mark.parametrize("n", [(162, 162, 162), (36, 32, 18)])
+def test_builders_on_ragged_tiles_and_many_atoms(torch, n):
+    L = (12.0, 12.0, 12.0)
+    rng = np.random.default_rng(41)
+    m = 300
+    xyz, q = rng.uniform(0.0, 12.0, (m, 3)), rng.normal(size=m)
+    radius, sigma = rng.uniform(0.3, 0.5, m), rng.uniform(0.3, 0.6, m)
+    p = dict(eps_inf=78.36, delta=0.1, exclusion=1, z_lim=0.1, delta_z=0.3)
+    N = n[0] * n[1] * n[2]
+    nodes = np.unique(np.r_[0:400, N - 400:N, rng.choice(N, 3000)])
+    s = _solver(torch, n, L)
+    s.build_epsilon(xyz, radius, p)
+    at = torch.from_numpy(nodes).cuda()
+    eps = _host(s.get_epsilon().reshape(-1)[at])
+    rho = _host(s.build_rho(xyz, q, sigma).reshape(-1)[at])
+    eps_ref = O.eps_erf(n, L, xyz, radius, p, nodes=nodes)
+    rho_ref = O.rho_gauss(n, L, xyz, q, sigma, nodes=nodes)
+    assert 10.0 < eps_ref.max() and eps_ref.min() < 1.01
+    # the bars of the slab's builders
+    assert np.abs(eps - eps_ref).max() <= 1e-12 * 78.36
+    assert np.abs(rho - rho_ref).max() <= 1e-12 * np.abs(rho_ref).max()
+
+
 # ---------------------------------------------------------------- full solve
 
 def _check_solution(torch, s, rho, eps, phi, E, info, tol_E, tol_phi):
