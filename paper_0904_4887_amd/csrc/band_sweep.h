@@ -31,6 +31,17 @@
 // eps (plane m + 1 is written while planes m - 1 and m are read) and 2 of the
 // first colour.
 //
+// PRO: u_in is the array uin plus the trilinear interpolation of the coarse
+// correction uc.  The coarse planes around the march pass through a ring of two
+// LDS slots (each thread loads 8 or 4 bytes of the next one with its plane), and
+// each plane's second-colour values, the only u_in values a sweep reads, take
+// the interpolation as they enter the registers.  Every weight is a power of
+// two and the order of the terms is that of the separate kernel, so the sums
+// are its sums bit for bit.  (The coarse rows straight from global memory into
+// each thread's registers cost 12 to 16 of them and spilled: 52 us a sweep
+// at 192 x 192 x 384 in float32, 70 at 144 x 144 x 288 in float64; now 38.7 and
+// 36.8, where the separate kernel took 16.0 and 18.9 besides 35.5 and 34.5.)
+//
 // The code is plain arithmetic and addressing on pointers so that a host
 // build can step it thread by thread; BAND_CHECK(i, n) is a bounds hook that
 // such a build defines.  It needs gs_value(off, f, diag) declared before it.
@@ -47,6 +58,10 @@ template <> struct BandVec<float, 4> { typedef float V __attribute__((ext_vector
 template <> struct BandVec<float, 2> { typedef float V __attribute__((ext_vector_type(2))); };
 template <> struct BandVec<double, 2> { typedef double V __attribute__((ext_vector_type(2))); };
 
+// A thread's part of a coarse plane (PRO): 2 / W of its vector of the fine one.
+template <class T, int W> struct BandCoarse { typedef T V; };
+template <> struct BandCoarse<float, 4> { typedef float V __attribute__((ext_vector_type(2))); };
+
 // Launch-wide parameters.
 template <class T> struct BandArgs {
     const T *uin;  // ghosted: plane k (-1 .. nw) at (k + 1) * nx * ny
@@ -62,11 +77,19 @@ template <class T> struct BandArgs {
     // being stored in uout
     T *zadd;
     int nzb, kw0;
+    // PRO: the coarse correction (ghosted, nx / 2 x ny / 2, its ghost planes
+    // zero), and whether z is coarsened too
+    const T *uc = nullptr;
+    int zc = 0;
 };
 
 // Elements of one block's LDS: u (2 slots), eps (3), first colour (2).
 __host__ __device__ inline int band_lds_elems(int nx, int ty) {
     return 2 * (ty + 4) * (nx / 2) + 3 * (ty + 4) * nx + 2 * (ty + 2) * (nx / 2);
+}
+// With PRO also two slots of (ty + 4) / 2 + 1 coarse rows.
+__host__ __device__ inline int band_lds_elems_pro(int nx, int ty) {
+    return band_lds_elems(nx, ty) + 2 * ((ty + 4) / 2 + 1) * (nx / 2);
 }
 
 template <class T>
@@ -81,7 +104,7 @@ __host__ __device__ __forceinline__ T band_point(T cx, T cy, T cz, T e0, T exp, 
 }
 
 // PD: planes loaded ahead (1 or 2; each costs 3 W-vectors of registers).
-template <class T, int W, bool ZIN, bool DOWN, int PD>
+template <class T, int W, bool ZIN, bool DOWN, int PD, bool PRO = false>
 struct BandSweep {
     typedef typename BandVec<T, W>::V V;
     static constexpr int H = W / 2;         // points of each colour in a vector
@@ -108,6 +131,13 @@ struct BandSweep {
     V E1, E2, E3, F1;
     T U0[H], U1[H], U2[H], E0[H], F0[H], R0[H], R1[H], R2[H];
     V PU[PD], PE[PD], PF[PD];  // loads in flight: set q = {u(q), eps(q), f(q - D)}, slot = step index % PD
+    // PRO: this thread's part of the coarse plane in flight; its byte offset in
+    // a coarse plane and its element in a slot; the ring
+    typedef typename BandCoarse<T, W>::V VC;
+    VC PC[PRO ? PD : 1];
+    unsigned oc;
+    int lc;
+    T *sc;
 
     // ring position of plane q: >= 0 for every plane used (k0 - 4 .. k1 + 3)
     __host__ __device__ __forceinline__ int lp(int q) const { return q - k0 + 4; }
@@ -147,6 +177,14 @@ struct BandSweep {
         of = (unsigned)(jf * a.nx + x0);
         par = (a.c0 - j) & 1;
         for (int i = 0; i < H; ++i) R0[i] = R1[i] = R2[i] = T(0);
+        if constexpr (PRO) {
+            constexpr int WC = sizeof(VC) / sizeof(T);
+            sc = sr + 2 * (a.ty + 2) * nh;
+            const int nc = coarse_rows() * nh, e = WC * tid < nc ? WC * tid : nc - WC;
+            const int row = e / nh, nyc = a.ny / 2;
+            lc = WC * tid < nc ? e : -1;
+            oc = (unsigned)((j0 / 2 - 1 + row + 2 * nyc) % nyc * nh + e - row * nh) * (unsigned)sizeof(T);
+        }
     }
 
     // second-colour columns of plane q: x0 + s + 2i
@@ -170,12 +208,81 @@ struct BandSweep {
         BAND_CHECK((size_t)k * plane + of + W - 1, (size_t)a.nw * plane);
         return *(const V *)(a.f + (size_t)k * plane + of);
     }
+    // PRO.  Coarse rows of a slot: those around the band rows; row l is coarse
+    // row j0 / 2 - 1 + l, and band row r lies on row r / 2 or half way to the next
+    __host__ __device__ __forceinline__ int coarse_rows() const { return (a.ty + 4) / 2 + 1; }
+    // coarse planes (ghosted index) around fine plane q, lower and upper (the
+    // same one where q lies on it)
+    __host__ __device__ __forceinline__ int clo(int q) const { return a.zc ? (q + 1) >> 1 : q + 1; }
+    __host__ __device__ __forceinline__ int chi(int q) const { return a.zc ? (q >> 1) + 1 : q + 1; }
+    // the one of the two that the march reaches last
+    __host__ __device__ __forceinline__ int cfar(int q) const { return DOWN ? clo(q) : chi(q); }
+    __host__ __device__ __forceinline__ VC ld_c(int cp) const {
+        const int hi = chi(qhi), p = cp < 0 ? 0 : (cp > hi ? hi : cp);
+        BAND_CHECK((size_t)p, (size_t)(a.zc ? (a.nw - 1) / 2 : a.nw) + 2);
+        BAND_CHECK(oc / sizeof(T) + sizeof(VC) / sizeof(T) - 1, (size_t)nh * (a.ny / 2));
+        return *(const VC *)((const char *)(a.uc + (size_t)p * nh * (a.ny / 2)) + oc);
+    }
+    __host__ __device__ __forceinline__ void stash_c(int cp, const VC &v) {
+        BAND_CHECK((cp & 1) * coarse_rows() * nh + (lc < 0 ? 0 : lc) + sizeof(VC) / sizeof(T) - 1,
+                   (size_t)2 * coarse_rows() * nh);
+        if (lc >= 0) *(VC *)(sc + (cp & 1) * coarse_rows() * nh + lc) = v;
+    }
+    // d (second-colour values of plane q, columns x0 + s + 2i) += interpolation:
+    // from the ring, and for the prologue's planes from global memory (every row
+    // loaded, with weight 0 where it does not count, so that no load waits for
+    // another)
+    __host__ __device__ __forceinline__ void add_row(T *t, const T *v, T w, int s) const {
+        for (int i = 0; i < H; ++i) t[i] += w * (s ? T(0.5) * (v[i] + v[i + 1]) : v[i]);
+    }
+    __host__ __device__ __forceinline__ void add_ring(T *d, int q, int s) const {
+        const T *lo = sc + (clo(q) & 1) * coarse_rows() * nh, *hi = sc + (chi(q) & 1) * coarse_rows() * nh;
+        const int r0 = (r >> 1) * nh, r1 = ((r + 1) >> 1) * nh, xn = x0 / 2 + H == nh ? 0 : x0 / 2 + H;
+        const bool zh = a.zc && !(q & 1), yh = r & 1;
+        const T w = (zh ? T(0.5) : T(1)) * (yh ? T(0.5) : T(1));
+        T t[H];
+        for (int i = 0; i < H; ++i) t[i] = T(0);
+        auto row = [&](const T *c) {
+            T v[H + 1];
+            for (int i = 0; i < H; ++i) v[i] = c[x0 / 2 + i];
+            v[H] = c[xn];
+            add_row(t, v, w, s);
+        };
+        row(lo + r0);
+        if (yh) row(lo + r1);
+        if (zh) {
+            row(hi + r0);
+            if (yh) row(hi + r1);
+        }
+        for (int i = 0; i < H; ++i) d[i] += t[i];
+    }
+    struct Coarse { T v[4][H + 1]; };
+    __host__ __device__ __forceinline__ void ld_rows(int q, Coarse &c) const {
+        const int k = q < qlo ? qlo : (q > qhi ? qhi : q), nyc = a.ny / 2;
+        const int xn = x0 / 2 + H == nh ? 0 : x0 / 2 + H;
+        for (int h = 0; h < 4; ++h) {
+            const int cp = h < 2 ? clo(k) : chi(k), row = (j0 / 2 - 1 + ((r + (h & 1)) >> 1) + 2 * nyc) % nyc;
+            BAND_CHECK((size_t)cp, (size_t)(a.zc ? (a.nw - 1) / 2 : a.nw) + 2);
+            const T *b = a.uc + ((size_t)cp * nyc + row) * nh;
+            for (int i = 0; i < H; ++i) c.v[h][i] = b[x0 / 2 + i];
+            c.v[h][H] = b[xn];
+        }
+    }
+    __host__ __device__ __forceinline__ void add_rows(T *d, const Coarse &c, int q, int s) const {
+        const bool zh = a.zc && !(q & 1), yh = r & 1;
+        const T w = (zh ? T(0.5) : T(1)) * (yh ? T(0.5) : T(1));
+        T t[H];
+        for (int i = 0; i < H; ++i) t[i] = T(0);
+        for (int h = 0; h < 4; ++h) add_row(t, c.v[h], (h & 1 && !yh) || (h & 2 && !zh) ? T(0) : w, s);
+        for (int i = 0; i < H; ++i) d[i] += t[i];
+    }
     // set q into prefetch slot s
     __host__ __device__ __forceinline__ void fetch(int q, int s) {
         if constexpr (ZIN) PU[s] = V(0);
         else PU[s] = ld_u(q);
         PE[s] = ld_e(q);
         PF[s] = ld_f(q - D);
+        if constexpr (PRO) PC[s] = ld_c(cfar(q + D));
     }
 
     // u ring: second-colour values of plane q (uc, as kept in registers), one
@@ -203,6 +310,14 @@ struct BandSweep {
     // first PD steps in flight.
     __host__ __device__ __forceinline__ void prologue() {
         const int m0 = first();
+        Coarse c1, c2;
+        VC cl, ch;
+        if constexpr (PRO) {
+            ld_rows(m0 - D, c1);
+            ld_rows(m0, c2);
+            cl = ld_c(clo(m0 + D));
+            ch = ld_c(chi(m0 + D));
+        }
         if constexpr (ZIN) {
             for (int i = 0; i < H; ++i) U0[i] = U1[i] = U2[i] = T(0);
         } else {
@@ -213,6 +328,12 @@ struct BandSweep {
         E2 = ld_e(m0 - D);
         E3 = ld_e(m0);
         F1 = ld_f(m0 - D);
+        if constexpr (PRO) {
+            add_rows(U1, c1, m0 - D, scol(m0 - D));
+            add_rows(U2, c2, m0, scol(m0));
+            stash_c(clo(m0 + D), cl);
+            stash_c(chi(m0 + D), ch);
+        }
         stash_u(m0, U2);
         stash_e(m0 - D, E2);
         stash_e(m0, E3);
@@ -237,6 +358,11 @@ struct BandSweep {
         half(F0, F1, p);
         for (int i = 0; i < H; ++i) { R0[i] = R1[i]; R1[i] = R2[i]; }
         if constexpr (!ZIN) half(U2, PU[B], p);
+        if constexpr (PRO) {
+            add_ring(U2, m + D, p);
+            // the plane that m + 2 D needs beyond those of m + D
+            if (!a.zc || ((m + D) & 1)) stash_c(cfar(m + 2 * D), PC[B]);
+        }
         E1 = E2; E2 = E3; E3 = PE[B];
         F1 = PF[B];
         stash_u(m + D, U2);

@@ -289,6 +289,12 @@ template <class T>
 bool launch_sweep_fused(hipStream_t s, const Level &L, const T *uin, T *uout, int first_color, bool zero_in,
                         bool tiles_only, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
                         T *zadd = nullptr, int nzb = 0, int kw0 = 0);
+// The row-band sweep of uin + (the trilinear interpolation of C's correction):
+// prolongation and first post-sweep in one pass; false, with nothing launched,
+// where the row-band sweep does not fit.
+template <class T>
+bool launch_sweep_prolong(hipStream_t s, const Level &L, const Level &C, const T *uin, T *uout, int first_color,
+                          hipEvent_t ev_start, hipEvent_t ev_stop, T *zadd, int nzb, int kw0);
 // The rest of a V-cycle from level l0 down, in one single-workgroup kernel.
 template <class T>
 void launch_vcycle_bottom(hipStream_t s, const std::vector<Level *> &levels, size_t l0, int pre, int post,

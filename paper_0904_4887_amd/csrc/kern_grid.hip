@@ -957,10 +957,12 @@ k_sweep_fused(const T *__restrict__ uin, T *__restrict__ uout, const T *__restri
 // it does not need), two otherwise.  One block of (ty + 4) * nx / W threads
 // per CU is the measured optimum at 192 x 192: capping registers for two
 // (six wavefronts per SIMD) spills and shortens the z chunks, 40 % slower.
-template <class T, int W, bool ZIN> constexpr int band_pd() { return ZIN || W == 2 ? 2 : 1; }
-template <class T, int W, bool ZIN, bool DOWN>
+template <class T, int W, bool ZIN, bool PRO> constexpr int band_pd() {
+    return (ZIN || W == 2) && !(PRO && sizeof(T) == 8) ? 2 : 1;
+}
+template <class T, int W, bool ZIN, bool DOWN, bool PRO>
 __device__ __forceinline__ void band_march(const BandArgs<T> &a, T *lds, int band, int chunk) {
-    BandSweep<T, W, ZIN, DOWN, band_pd<T, W, ZIN>()> b;
+    BandSweep<T, W, ZIN, DOWN, band_pd<T, W, ZIN, PRO>(), PRO> b;
     b.init(a, lds, band, chunk, threadIdx.x);
     b.prologue();
     __syncthreads();
@@ -979,7 +981,7 @@ __device__ __forceinline__ void band_march(const BandArgs<T> &a, T *lds, int ban
 // each XCD receives covers a few neighbouring bands over a run of neighbouring
 // chunks, whose shared halo rows and planes then meet in that XCD's L2.  Odd
 // chunks march down, even ones up.
-template <class T, int W, bool ZIN>
+template <class T, int W, bool ZIN, bool PRO = false>
 __global__ void __launch_bounds__(1024) k_sweep_band(BandArgs<T> a, int nb_real, int gb) {
     extern __shared__ __align__(16) unsigned char band_lds[];
     const int t = xcd_tile(nb_real);
@@ -988,8 +990,8 @@ __global__ void __launch_bounds__(1024) k_sweep_band(BandArgs<T> a, int nb_real,
     const int g = t / (gb * nchunks), q = t - g * gb * nchunks;
     const int chunk = q / gb, band = g * gb + (q - (q / gb) * gb);
     T *lds = reinterpret_cast<T *>(band_lds);
-    if (chunk & 1) band_march<T, W, ZIN, true>(a, lds, band, chunk);
-    else band_march<T, W, ZIN, false>(a, lds, band, chunk);
+    if (chunk & 1) band_march<T, W, ZIN, true, PRO>(a, lds, band, chunk);
+    else band_march<T, W, ZIN, false, PRO>(a, lds, band, chunk);
 }
 
 // ---------------------------------------------------------------- residual + restriction
@@ -2112,15 +2114,15 @@ static int band_rows(const Level &L) {
         if (band_rows_fit<T, W>(L, t)) return t;
     return 0;
 }
-template <class T, int W, bool ZIN>
-static bool sweep_band_w(hipStream_t s, const Level &L, const T *uin, T *uout, int first_color, int ty,
-                         hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr, T *zadd = nullptr, int nzb = 0,
-                         int kw0 = 0) {
-    if (ty == 0) ty = band_rows<T, W>(L);
-    if (ty == 0 || !band_rows_fit<T, W>(L, ty)) return false;
+template <class T, int W, bool ZIN, bool PRO = false>
+static bool sweep_band_w(hipStream_t s, const Level &L, const T *uin, T *uout, int first_color, hipEvent_t e0,
+                         hipEvent_t e1, T *zadd, int nzb, int kw0, const Level *C = nullptr) {
+    const int ty = band_rows<T, W>(L);
+    if (ty == 0) return false;
     const int nt = (ty + 4) * (L.nx / W);
-    const size_t bytes = sizeof(T) * (size_t)band_lds_elems(L.nx, ty);
-    const int per = occupancy(reinterpret_cast<const void *>(&k_sweep_band<T, W, ZIN>), nt, bytes);
+    const size_t bytes = sizeof(T) * (size_t)(PRO ? band_lds_elems_pro(L.nx, ty) : band_lds_elems(L.nx, ty));
+    if (bytes > BOTTOM_LDS_BYTES) return false;
+    const int per = occupancy(reinterpret_cast<const void *>(&k_sweep_band<T, W, ZIN, PRO>), nt, bytes);
     if (per < 1) return false;
     const int bands = L.ny / ty;
     const long slots = (long)cu_count() * per;
@@ -2137,8 +2139,8 @@ static bool sweep_band_w(hipStream_t s, const Level &L, const T *uin, T *uout, i
     const bool f32 = sizeof(T) == 4;
     BandArgs<T> a{uin, uout, L.eps.as<T>(), L.f.as<T>(), L.nx, L.ny, L.nw, ty, bands, kc, first_color,
                   (T)(f32 ? la.cxf : la.cx), (T)(f32 ? la.cyf : la.cy), (T)(f32 ? la.czf : la.cz),
-                  zadd, nzb, kw0};
-    hipExtLaunchKernelGGL(k_sweep_band<T, W, ZIN>, dim3(padded), dim3(nt), (uint32_t)bytes, s, e0, e1, 0, a, nb, gb);
+                  zadd, nzb, kw0, PRO ? C->u.as<T>() : nullptr, PRO && C->zc ? 1 : 0};
+    hipExtLaunchKernelGGL((k_sweep_band<T, W, ZIN, PRO>), dim3(padded), dim3(nt), (uint32_t)bytes, s, e0, e1, 0, a, nb, gb);
     DWP_LAUNCH_CHECK();
     return true;
 }
@@ -2158,8 +2160,22 @@ bool sweep_band_fits<double>(const Level &L) {
 template <class T, int W>
 static bool sweep_band_z(hipStream_t s, const Level &L, const T *uin, T *uout, int first_color, bool zero_in,
                          hipEvent_t e0, hipEvent_t e1, T *zadd, int nzb, int kw0) {
-    return zero_in ? sweep_band_w<T, W, true>(s, L, uin, uout, first_color, 0, e0, e1, zadd, nzb, kw0)
-                   : sweep_band_w<T, W, false>(s, L, uin, uout, first_color, 0, e0, e1, zadd, nzb, kw0);
+    return zero_in ? sweep_band_w<T, W, true>(s, L, uin, uout, first_color, e0, e1, zadd, nzb, kw0)
+                   : sweep_band_w<T, W, false>(s, L, uin, uout, first_color, e0, e1, zadd, nzb, kw0);
+}
+// The row-band sweep of u + (the interpolation of C's correction); returns
+// false, with nothing launched, where the row-band kernel does not fit.
+template <>
+bool launch_sweep_prolong<float>(hipStream_t s, const Level &L, const Level &C, const float *uin, float *uout,
+                                 int first_color, hipEvent_t e0, hipEvent_t e1, float *zadd, int nzb, int kw0) {
+    return L.nx % 4 == 0
+               ? sweep_band_w<float, 4, false, true>(s, L, uin, uout, first_color, e0, e1, zadd, nzb, kw0, &C)
+               : sweep_band_w<float, 2, false, true>(s, L, uin, uout, first_color, e0, e1, zadd, nzb, kw0, &C);
+}
+template <>
+bool launch_sweep_prolong<double>(hipStream_t s, const Level &L, const Level &C, const double *uin, double *uout,
+                                  int first_color, hipEvent_t e0, hipEvent_t e1, double *zadd, int nzb, int kw0) {
+    return sweep_band_w<double, 2, false, true>(s, L, uin, uout, first_color, e0, e1, zadd, nzb, kw0, &C);
 }
 // Returns whether the sweep added its output into zadd (the row-band kernel
 // did); otherwise it is in uout.

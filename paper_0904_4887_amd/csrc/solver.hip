@@ -424,9 +424,27 @@ bool vcycle(dwp_ctx *c, size_t l, bool u_unset, T *zadd) {
              launch_resid_restrict<T>(s, L, C));
     }
     vcycle<T>(c, l + 1, false, nullptr);
-    PROF(c, PG_MG_OTHER, ts * (C.n_interior() + 2.0 * L.n_interior()), launch_prolong_add<T>(s, L, C));
     // the last sweep may add its result straight into zadd
-    for (int k = 0; k < c->opts.post; ++k) smooth(1, k + 1 == c->opts.post ? zadd : nullptr);
+    auto za = [&](int k) { return k + 1 == c->opts.post ? zadd : nullptr; };
+    int k = 0;
+    // the row-band sweep interpolates the coarse correction as it reads u, at
+    // every level it takes (prolongation and first post-sweep apart and fused,
+    // us: 51.5 and 38.7 at 192 x 192 x 255 points in float32, 20.4 and 15.5 at
+    // 96 x 96 x 127 in float64, 11.3 and 9.9 on levels of 24 x 24)
+    if (fused && c->opts.smoother == 1 && c->opts.post > 0 && sweep_band_fits<T>(L)) {
+        const int ev = c->prof.reserve(sg);
+        if (launch_sweep_prolong<T>(s, L, C, L.u.as<T>(), L.u2.as<T>(), 1, c->prof.event(ev, 0), c->prof.event(ev, 1),
+                                    za(0), p.nz, p.k_w0)) {
+            added = za(0) != nullptr;
+            c->prof.done(ev, sg, 2.0 * pass_bytes + (added ? 0.5 * pass_bytes : 0.0) + ts * (double)C.n_interior());
+            std::swap(L.u.p, L.u2.p);
+            zero_in = false;
+            k = 1;
+        }
+    }
+    if (k == 0)
+        PROF(c, PG_MG_OTHER, ts * (C.n_interior() + 2.0 * L.n_interior()), launch_prolong_add<T>(s, L, C));
+    for (; k < c->opts.post; ++k) smooth(1, za(k));
     return added;
 }
 
