@@ -340,15 +340,25 @@ void launch_scaled_product(hipStream_t s, const Plan &p, const double *gr, const
 // kern_fft.hip
 // symbol of the operator of the given order (2: 7-point, 6: Eq. 18) along one axis
 void fft_plan_axis(FFTAxis &ax, int n, double h, bool half, int order);
+// A rescaling that is left to the next reader of a new Krylov vector: nu^2 is
+// the sum of nparts block partials (to be stored at *nu2), and the vector is
+// divided by nu, in place, unless nu is 0 or within tol of 1.
+struct Rescale {
+    const double *partial = nullptr;  // none when null
+    int nparts = 0;
+    double *nu2 = nullptr;
+    double tol = 0.0;
+};
 // out = s .* L^{-1} (s .* r) (s == nullptr: unscaled), zero mean; fp32: the
-// spectrum (cbuf, sized for float64) and the transforms in float32
+// spectrum (cbuf, sized for float64) and the transforms in float32; rs: r is
+// rescaled first (and written back)
 void launch_vacuum_solve(hipStream_t st, const Plan &p, const FFTAxis &ax, const FFTAxis &ay,
-                         const FFTAxis &az, const double *r, const double *sinv, void *cbuf,
-                         double *out, Profiler *prof, bool fp32);
+                         const FFTAxis &az, double *r, const double *sinv, void *cbuf,
+                         double *out, Profiler *prof, bool fp32, const Rescale &rs = {});
 // the same from a float32 Krylov basis vector to a float32 preconditioned one
 void launch_vacuum_solve(hipStream_t st, const Plan &p, const FFTAxis &ax, const FFTAxis &ay,
-                         const FFTAxis &az, const float *r, const double *sinv, void *cbuf,
-                         float *out, Profiler *prof, bool fp32);
+                         const FFTAxis &az, float *r, const double *sinv, void *cbuf,
+                         float *out, Profiler *prof, bool fp32, const Rescale &rs = {});
 // and from a float16 one
 void launch_vacuum_solve(hipStream_t st, const Plan &p, const FFTAxis &ax, const FFTAxis &ay,
                          const FFTAxis &az, const _Float16 *r, const double *sinv, void *cbuf,
@@ -367,8 +377,9 @@ void launch_axpy_multi(hipStream_t s, double *w, const double *V, size_t ldv, in
 bool orth_update_supported(const double *V, size_t ldv, int nv, size_t n);
 // mean_free: w is an operator output whose mean must go too (its sum at hc[67]
 // from launch_multidot_sum); the constant direction is removed in the same pass
+// With rs the rescaling is described there and left to the caller.
 void launch_orth_update(hipStream_t s, double *w, const double *V, size_t ldv, int nv, double *hc, size_t n,
-                        double *partial, bool mean_free = false);
+                        double *partial, bool mean_free = false, Rescale *rs = nullptr);
 // the projection of launch_multidot (nv <= 16, 16-byte aligned) with the sum of
 // w's elements into *sum_out as well
 void launch_multidot_sum(hipStream_t s, const double *V, size_t ldv, int nv, const double *w, size_t n,
@@ -384,7 +395,7 @@ constexpr int GRAM_SLOT = 20;
 void launch_multidot32(hipStream_t s, const float *V, size_t ldv, int nv, const float *w, size_t n, double *partial,
                        double *out, double *norm_out);
 void launch_orth_update32(hipStream_t s, float *w, const float *V, size_t ldv, int nv, double *hc, size_t n,
-                          double *partial, bool mean_free = false);
+                          double *partial, bool mean_free = false, Rescale *rs = nullptr);
 // the float32 projection with the sum of w as well (mean-free Arnoldi step)
 void launch_multidot32_sum(hipStream_t s, const float *V, size_t ldv, int nv, const float *w, size_t n,
                            double *partial, double *out, double *norm_out, double *sum_out);

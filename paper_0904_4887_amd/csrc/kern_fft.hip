@@ -286,6 +286,27 @@ __device__ __forceinline__ void load_batched(int n_el, Ld ld, St st, const V *__
 }
 constexpr int FFT_KL = FFT_MAXE / FFT_THREADS;  // one batch covers a block of the separate passes
 
+// ---------------------------------------------------------------- rescaling of the input
+// The divisor's reciprocal of a pending rescaling (0: none), in every thread;
+// the partials are added in the order of the separate kernel (256 threads, then
+// four waves).  sh: four doubles.
+__device__ double rescale_factor(const Rescale &rs, double *sh) {
+    double v = 0.0;
+    if (threadIdx.x < RED_THREADS)
+        for (int b = threadIdx.x; b < rs.nparts; b += RED_THREADS) v += rs.partial[b];
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    if (threadIdx.x < RED_THREADS && (threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double tot = 0.0;
+    for (int q = 0; q < RED_THREADS / 64; ++q) tot += sh[q];
+    if (blockIdx.x == 0 && threadIdx.x == 0) *rs.nu2 = tot;
+    const double nu = sqrt(tot);
+    return nu == 0.0 || fabs(nu - 1.0) <= rs.tol ? 0.0 : 1.0 / nu;
+}
+template <class V> __device__ __forceinline__ void rescale(V &v, double f, int n) {
+    for (int q = 0; q < n; ++q) v[q] = (decltype(v[q] + v[q]))((double)v[q] * f);
+}
+
 // ---------------------------------------------------------------- x passes
 // Rows are the nx-long x lines of the [nz][ny][nx] grid; B = 2^lb complex
 // lines per block carry 2B real rows.  LDS lines are padded to n + 1 elements.
@@ -295,11 +316,11 @@ constexpr int FFT_KL = FFT_MAXE / FFT_THREADS;  // one batch covers a block of t
 // same way (value by value: 47.6 us, now 42.0 us at 192 x 192 x 384 from float32).
 template <class S, class TI, bool R6, bool SC, int W>
 __global__ void __launch_bounds__(FFT_THREADS)
-k_fft_x_fwd(const TI *__restrict__ in, const double *__restrict__ sinv, cplx<S> *__restrict__ out,
+k_fft_x_fwd(TI *in, const double *__restrict__ sinv, cplx<S> *__restrict__ out,
             Radices rd, const cplx<S> *__restrict__ tw, int lb, int nrows, int nkx, int ldc, Div dw, Div dk,
-            Div dk2) {
+            Div dk2, Rescale rs) {
     using C = cplx<S>;
-    typedef TI TIW __attribute__((ext_vector_type(W)));
+    typedef std::remove_const_t<TI> TIW __attribute__((ext_vector_type(W)));
     typedef double DW __attribute__((ext_vector_type(W)));
     extern __shared__ __align__(16) unsigned char lds_raw[];
     C *lds = reinterpret_cast<C *>(lds_raw);
@@ -310,6 +331,9 @@ k_fft_x_fwd(const TI *__restrict__ in, const double *__restrict__ sinv, cplx<S> 
         const int nw = n / W;  // dw divides by it
         for (int e = threadIdx.x; e < n; e += FFT_THREADS) twl[e] = tw[e];
         constexpr int KV = SC ? 2 : (FFT_MAXE / W + FFT_THREADS - 1) / FFT_THREADS;
+        constexpr bool RS = !std::is_const<TI>::value;  // a float16 vector comes out unit
+        double *rsh = reinterpret_cast<double *>(twl + n);
+        double fac = 0.0;
         for (int e0 = 0; e0 < B * nw; e0 += KV * FFT_THREADS) {
             TIW va[KV], vb[KV];
             DW sa[SC ? KV : 1], sb[SC ? KV : 1];
@@ -330,6 +354,25 @@ k_fft_x_fwd(const TI *__restrict__ in, const double *__restrict__ sinv, cplx<S> 
                     } else {
                         va[m] = vb[m] = TIW(0);
                         if constexpr (SC) sa[m] = sb[m] = DW(0);
+                    }
+                }
+            }
+            if constexpr (RS) {
+                if (rs.partial) {
+                    if (e0 == 0) fac = rescale_factor(rs, rsh);
+                    if (fac != 0.0) {
+#pragma unroll
+                        for (int m = 0; m < KV; ++m) {
+                            const int e = e0 + threadIdx.x + m * FFT_THREADS;
+                            if (e >= B * nw) continue;
+                            const int l = udiv(e, dw), t = e - l * nw, ra = r0 + 2 * l;
+                            if (ra + 1 >= nrows) continue;
+                            TI *x = in + (size_t)ra * n + W * t;
+                            rescale(va[m], fac, W);
+                            rescale(vb[m], fac, W);
+                            *reinterpret_cast<TIW *>(x) = va[m];
+                            *reinterpret_cast<TIW *>(x + n) = vb[m];
+                        }
                     }
                 }
             }
@@ -593,12 +636,12 @@ k_fft_y(cplx<S> *__restrict__ c, Radices rd, const cplx<S> *__restrict__ tw, int
 // CU and nothing to overlap with.)
 template <class S, class TI, bool SC, int NT, int PE>
 __global__ void __launch_bounds__(NT)
-k_fft_xy_fwd(const TI *__restrict__ in, const double *__restrict__ sinv, cplx<S> *__restrict__ out, Radices rx,
+k_fft_xy_fwd(TI *in, const double *__restrict__ sinv, cplx<S> *__restrict__ out, Radices rx,
              Radices ry, const cplx<S> *__restrict__ twx, const cplx<S> *__restrict__ twy, int ldc, Div dl, Div dw,
-             Div dk) {
+             Div dk, Rescale rs) {
     using C = cplx<S>;
     constexpr int MAXE = PE * NT;
-    typedef TI TIW __attribute__((ext_vector_type(2)));
+    typedef std::remove_const_t<TI> TIW __attribute__((ext_vector_type(2)));
     typedef double DW __attribute__((ext_vector_type(2)));
     extern __shared__ __align__(16) unsigned char lds_raw[];
     C *lds = reinterpret_cast<C *>(lds_raw);
@@ -622,6 +665,24 @@ k_fft_xy_fwd(const TI *__restrict__ in, const double *__restrict__ sinv, cplx<S>
                 if constexpr (SC) {
                     sa[m] = *reinterpret_cast<const DW *>(sinv + ia);
                     sb[m] = *reinterpret_cast<const DW *>(sinv + ia + n);
+                }
+            }
+        }
+        if constexpr (!std::is_const<TI>::value) {  // a float16 vector comes out unit
+            if (rs.partial) {
+                const double fac = rescale_factor(rs, reinterpret_cast<double *>(ty + ny));
+                if (fac != 0.0) {
+#pragma unroll
+                    for (int m = 0; m < KV; ++m) {
+                        const int e = threadIdx.x + m * NT;
+                        if (e >= nl * nw) continue;
+                        const int l = udiv(e, dw), t = e - l * nw;
+                        TI *x = in + (z * ny + 2 * l) * n + 2 * t;
+                        rescale(va[m], fac, 2);
+                        rescale(vb[m], fac, 2);
+                        *reinterpret_cast<TIW *>(x) = va[m];
+                        *reinterpret_cast<TIW *>(x + n) = vb[m];
+                    }
                 }
             }
         }
@@ -935,7 +996,7 @@ void fft_plan_axis(FFTAxis &ax, int n, double h, bool half, int order) {
 
 template <class S, class TI, class TO>
 static void vacuum_solve_t(hipStream_t st, const Plan &p, const FFTAxis &ax, const FFTAxis &ay, const FFTAxis &az,
-                           const TI *r, const double *sinv, void *cbuf_v, TO *out, Profiler *prof) {
+                           TI *r, const double *sinv, void *cbuf_v, TO *out, Profiler *prof, const Rescale &rs) {
     using C = cplx<S>;
     C *cbuf = static_cast<C *>(cbuf_v);
     auto TW = [](const FFTAxis &a) { return sizeof(S) == 8 ? a.tw.as<C>() : a.tw32.as<C>(); };
@@ -962,7 +1023,8 @@ static void vacuum_solve_t(hipStream_t st, const Plan &p, const FFTAxis &ax, con
     const int lbx = tile_log2(p.nx, budget(ax, sizeof(S) == 4 ? FFT_BUDGET_X32 : FFT_BUDGET_X, FFT_THREADS));
     const int Bx = 1 << lbx;
     const int gx = (nrows + 2 * Bx - 1) / (2 * Bx);
-    const size_t ldsx = sizeof(C) * ((size_t)Bx * (p.nx + 1) + p.nx);
+    constexpr size_t RSB = sizeof(double) * (RED_THREADS / 64);  // of a pending rescaling
+    const size_t ldsx = sizeof(C) * ((size_t)Bx * (p.nx + 1) + p.nx) + RSB;
     constexpr int KN = 16 / sizeof(C);
     const Div dk = make_div(p.nkx), dk2 = make_div((p.nkx + 1) / 2), dkn = make_div((p.nkx + KN - 1) / KN);
     // the variant of an x pass: scaled or not, rows of 4 m or 4 m + 2 values
@@ -989,7 +1051,7 @@ static void vacuum_solve_t(hipStream_t st, const Plan &p, const FFTAxis &ax, con
     };
     // both passes of a plane in one block
     const int pv = std::max(p.ny / 2 * (p.nx + 1), p.ny * p.nkx);
-    const size_t ldsp = sizeof(C) * ((size_t)pv + p.nx + p.ny);
+    const size_t ldsp = sizeof(C) * ((size_t)pv + p.nx + p.ny) + RSB;
     const bool plane = plane_pass(pv, ldsp, p.nz);
     const Div dl = make_div(p.ny / 2), dw2 = make_div(p.nx / 2);
     auto with_plane = [&](auto &&f) {
@@ -1009,7 +1071,7 @@ static void vacuum_solve_t(hipStream_t st, const Plan &p, const FFTAxis &ax, con
         static std::atomic<unsigned> attr{0};
         lds_attr(fptr(&k_fft_xy_fwd<S, TI, SC, NT, PE>), attr, ldsp);
         k_fft_xy_fwd<S, TI, SC, NT, PE><<<p.nz, NT, ldsp, st>>>(r, sinv, cbuf, RD(ax), RD(ay), TW(ax), TW(ay), p.ldc, dl,
-                                                            dw2, dk);
+                                                            dw2, dk, rs);
         DWP_LAUNCH_CHECK();
     });
     else with6(has6(ax), [&](auto r6) {
@@ -1019,7 +1081,7 @@ static void vacuum_solve_t(hipStream_t st, const Plan &p, const FFTAxis &ax, con
             static std::atomic<unsigned> attr{0};
             lds_attr(fptr(&k_fft_x_fwd<S, TI, R6, SC, W>), attr, ldsx);
             k_fft_x_fwd<S, TI, R6, SC, W><<<gx, FFT_THREADS, ldsx, st>>>(r, sinv, cbuf, RD(ax), TW(ax), lbx, nrows,
-                                                                        p.nkx, p.ldc, make_div(p.nx / W), dk, dk2);
+                                                                        p.nkx, p.ldc, make_div(p.nx / W), dk, dk2, rs);
             DWP_LAUNCH_CHECK();
         });
     });
@@ -1078,19 +1140,21 @@ static void vacuum_solve_t(hipStream_t st, const Plan &p, const FFTAxis &ax, con
 }
 
 void launch_vacuum_solve(hipStream_t st, const Plan &p, const FFTAxis &ax, const FFTAxis &ay, const FFTAxis &az,
-                         const double *r, const double *sinv, void *cbuf, double *out, Profiler *prof, bool fp32) {
-    if (fp32) vacuum_solve_t<float, double, double>(st, p, ax, ay, az, r, sinv, cbuf, out, prof);
-    else vacuum_solve_t<double, double, double>(st, p, ax, ay, az, r, sinv, cbuf, out, prof);
+                         double *r, const double *sinv, void *cbuf, double *out, Profiler *prof, bool fp32,
+                         const Rescale &rs) {
+    if (fp32) vacuum_solve_t<float, double, double>(st, p, ax, ay, az, r, sinv, cbuf, out, prof, rs);
+    else vacuum_solve_t<double, double, double>(st, p, ax, ay, az, r, sinv, cbuf, out, prof, rs);
 }
 void launch_vacuum_solve(hipStream_t st, const Plan &p, const FFTAxis &ax, const FFTAxis &ay, const FFTAxis &az,
-                         const float *r, const double *sinv, void *cbuf, float *out, Profiler *prof, bool fp32) {
-    if (fp32) vacuum_solve_t<float, float, float>(st, p, ax, ay, az, r, sinv, cbuf, out, prof);
-    else vacuum_solve_t<double, float, float>(st, p, ax, ay, az, r, sinv, cbuf, out, prof);
+                         float *r, const double *sinv, void *cbuf, float *out, Profiler *prof, bool fp32,
+                         const Rescale &rs) {
+    if (fp32) vacuum_solve_t<float, float, float>(st, p, ax, ay, az, r, sinv, cbuf, out, prof, rs);
+    else vacuum_solve_t<double, float, float>(st, p, ax, ay, az, r, sinv, cbuf, out, prof, rs);
 }
 void launch_vacuum_solve(hipStream_t st, const Plan &p, const FFTAxis &ax, const FFTAxis &ay, const FFTAxis &az,
                          const _Float16 *r, const double *sinv, void *cbuf, float *out, Profiler *prof, bool fp32) {
-    if (fp32) vacuum_solve_t<float, _Float16, float>(st, p, ax, ay, az, r, sinv, cbuf, out, prof);
-    else vacuum_solve_t<double, _Float16, float>(st, p, ax, ay, az, r, sinv, cbuf, out, prof);
+    if (fp32) vacuum_solve_t<float, const _Float16, float>(st, p, ax, ay, az, r, sinv, cbuf, out, prof, Rescale{});
+    else vacuum_solve_t<double, const _Float16, float>(st, p, ax, ay, az, r, sinv, cbuf, out, prof, Rescale{});
 }
 
 }  // namespace dwp

@@ -449,13 +449,17 @@ bool vcycle(dwp_ctx *c, size_t l, bool u_unset, T *zadd) {
 }
 
 template <class T, class TV, class TZ>
-void split_impl(dwp_ctx *c, const TV *v, TZ *z) {
+void split_impl(dwp_ctx *c, TV *v, TZ *z, const Rescale &rs) {
     Plan &p = c->plan;
     hipStream_t s = c->stream;
     const bool scaled = c->opts.scaled_dry != 0;
     c->phases.mark(s, PH_FFT);
-    launch_vacuum_solve(s, p, c->fx, c->fy, c->fz, v, scaled ? c->sinv.as<double>() : nullptr, c->cbuf.p, z,
-                        &c->prof, c->opts.fft_fp32 != 0);
+    const double *sinv = scaled ? c->sinv.as<double>() : nullptr;
+    constexpr bool half = std::is_const<TV>::value;  // a float16 vector is unit already
+    if constexpr (half)
+        launch_vacuum_solve(s, p, c->fx, c->fy, c->fz, v, sinv, c->cbuf.p, z, &c->prof, c->opts.fft_fp32 != 0);
+    else
+        launch_vacuum_solve(s, p, c->fx, c->fy, c->fz, v, sinv, c->cbuf.p, z, &c->prof, c->opts.fft_fp32 != 0, rs);
     c->phases.mark(s, PH_MG);
     if (c->opts.cycles == 0) {  // no wet correction: the split is the dry update alone
         c->phases.mark(s, PH_KRYLOV);
@@ -463,7 +467,7 @@ void split_impl(dwp_ctx *c, const TV *v, TZ *z) {
     }
     Level &F = *p.levels[0];
     const double nW = (double)F.n_interior();
-    if constexpr (std::is_same<TV, _Float16>::value) {
+    if constexpr (half) {
         PROF(c, PG_WET, (6.0 + sizeof(TZ) + sizeof(T)) * nW,
              launch_wet_residual_v16<T>(s, p, v, z, c->eps32.as<float>(), F.f.as<T>()));
     } else if constexpr (sizeof(TV) == 4) {
@@ -488,15 +492,18 @@ void split_impl(dwp_ctx *c, const TV *v, TZ *z) {
     c->phases.mark(s, PH_KRYLOV);
 }
 
-void apply_split(dwp_ctx *c, const double *v, double *z) {
-    if (c->opts.precision == DWP_MIXED) split_impl<float, double, double>(c, v, z);
-    else split_impl<double, double, double>(c, v, z);
+// rs: v is rescaled, in place, as the dry update reads it
+void apply_split(dwp_ctx *c, double *v, double *z, const Rescale &rs = {}) {
+    if (c->opts.precision == DWP_MIXED) split_impl<float, double, double>(c, v, z, rs);
+    else split_impl<double, double, double>(c, v, z, rs);
 }
 // the split of a float32 (float16) Krylov vector into a float32 one (mixed
 // precision, second order): z is rounded to float32 where it is stored, and
 // the Krylov method uses the stored z as it is
-void apply_split(dwp_ctx *c, const float *v, float *z) { split_impl<float, float, float>(c, v, z); }
-void apply_split(dwp_ctx *c, const _Float16 *v, float *z) { split_impl<float, _Float16, float>(c, v, z); }
+void apply_split(dwp_ctx *c, float *v, float *z, const Rescale &rs) { split_impl<float, float, float>(c, v, z, rs); }
+void apply_split(dwp_ctx *c, const _Float16 *v, float *z) {
+    split_impl<float, const _Float16, float>(c, v, z, Rescale{});
+}
 
 void check_finite_dev(dwp_ctx *c, const double *x, const char *what) {
     int *flags = reinterpret_cast<int *>(c->partial.as<double>());
@@ -661,9 +668,15 @@ int fgmres(dwp_ctx *c, const double *b, double bnorm, double *x, int *restarts, 
             if (hn == 0.0 || std::fabs(g[j + 1]) <= target) stop = true;
         };
         int steps = 0;
+        Rescale rs;  // pending for the next step's vector
         for (int j = 0; j < mm && !stop; ++j) {
             double *Vj = V + (size_t)j * N, *Vn = V + (size_t)(j + 1) * N, *Zj = Z + (size_t)j * N;
             double *hc = Hd + (size_t)j * HESS_STRIDE;
+            // the host reads the column after this step; otherwise the next
+            // step's dry update rescales the new vector as it reads it (a
+            // launch of its own: 4 us, and 14 at 192 x 192 x 384)
+            const bool read = j + 1 >= check_from || j + 1 == mm;
+            Rescale next, *defer = read ? nullptr : &next;
             if (v16) {
                 // v_j (float16) -> z_j; w = A z_j into vcur (float32);
                 // project on the float16 basis; the normalised vector into
@@ -679,7 +692,7 @@ int fgmres(dwp_ctx *c, const double *b, double bnorm, double *x, int *restarts, 
                                           N));
             } else if (v32) {
                 float *Vj32 = V32 + (size_t)j * N, *Vn32 = V32 + (size_t)(j + 1) * N, *Zj32 = Z32 + (size_t)j * N;
-                apply_split(c, (const float *)Vj32, Zj32);
+                apply_split(c, Vj32, Zj32, rs);
                 fused[j] = 1;  // restart <= 16 is checked with the options
                 if (six) {
                     // the adjoint's directions stay mean-free; A6 (A6^T) z without
@@ -690,17 +703,17 @@ int fgmres(dwp_ctx *c, const double *b, double bnorm, double *x, int *restarts, 
                                            c->transposed));
                     PROF(c, PG_MULTIDOT, 4.0 * N * (j + 2),
                          launch_multidot32_sum(s, V32, N, j + 1, Vn32, N, part, hc, hc + 64, hc + 67));
-                    PROF(c, PG_AXPY, 4.0 * N * (j + 3), launch_orth_update32(s, Vn32, V32, N, j + 1, hc, N, part, true));
+                    PROF(c, PG_AXPY, 4.0 * N * (j + 3), launch_orth_update32(s, Vn32, V32, N, j + 1, hc, N, part, true, defer));
                 } else {
                     // A z (float64 arithmetic, float32 out), then the projection and update on float32 vectors
                     PROF(c, PG_APPLY, 12.0 * N,
                          launch_apply_full_f32(s, p, (const float *)Zj32, c->eps32.as<float>(), Vn32));
                     PROF(c, PG_MULTIDOT, 4.0 * N * (j + 2),
                          launch_multidot32(s, V32, N, j + 1, Vn32, N, part, hc, hc + 64));
-                    PROF(c, PG_AXPY, 4.0 * N * (j + 3), launch_orth_update32(s, Vn32, V32, N, j + 1, hc, N, part));
+                    PROF(c, PG_AXPY, 4.0 * N * (j + 3), launch_orth_update32(s, Vn32, V32, N, j + 1, hc, N, part, false, defer));
                 }
             } else {
-                apply_split(c, Vj, Zj);
+                apply_split(c, Vj, Zj, rs);
                 if (c->transposed) {
                     // A6^T does not annihilate the constants (A6 does): keep the
                     // iterate in the zero-mean space where the adjoint is posed
@@ -718,11 +731,11 @@ int fgmres(dwp_ctx *c, const double *b, double bnorm, double *x, int *restarts, 
                                        c->transposed));
                     PROF(c, PG_MULTIDOT, md,
                          launch_multidot_sum(s, V, N, j + 1, Vn, N, part, hc, hc + 64, hc + 67));
-                    PROF(c, PG_AXPY, ax, launch_orth_update(s, Vn, V, N, j + 1, hc, N, part, true));
+                    PROF(c, PG_AXPY, ax, launch_orth_update(s, Vn, V, N, j + 1, hc, N, part, true, defer));
                 } else if (fused[j]) {
                     apply_operator(c, Zj, nullptr, Vn, false);
                     PROF(c, PG_MULTIDOT, md, launch_multidot(s, V, N, j + 1, Vn, N, part, hc, hc + 64));
-                    PROF(c, PG_AXPY, ax, launch_orth_update(s, Vn, V, N, j + 1, hc, N, part));
+                    PROF(c, PG_AXPY, ax, launch_orth_update(s, Vn, V, N, j + 1, hc, N, part, false, defer));
                 } else {
                     apply_operator(c, Zj, nullptr, Vn, false);
                     PROF(c, PG_MULTIDOT, md, launch_multidot(s, V, N, j + 1, Vn, N, part, hc, hc + 64));
@@ -730,8 +743,9 @@ int fgmres(dwp_ctx *c, const double *b, double bnorm, double *x, int *restarts, 
                     PROF(c, PG_VEC, 16.0 * N, launch_scale_dev(s, Vn, nullptr, hc + 65, N, 0));
                 }
             }
+            rs = next;
             steps = j + 1;
-            if (steps >= check_from || steps == mm) {
+            if (read) {
                 // read the columns not yet folded and fold them
                 const int n_new = steps - k;
                 DWP_HIP(hipMemcpyAsync(c->host, Hd + (size_t)k * HESS_STRIDE, sizeof(double) * HESS_STRIDE * n_new,
@@ -1580,7 +1594,8 @@ int dwp_vacuum_solve(dwp_ctx *c, const double *r, double *out) {
     dwp::need_grid(c);
     if (!r || !out) dwp::fail(DWP_EINVAL, "NULL pointer");
     DWP_HIP(hipSetDevice(c->device));
-    dwp::launch_vacuum_solve(c->stream, c->plan, c->fx, c->fy, c->fz, r, nullptr, c->cbuf.p, out,
+    // without a rescaling the right-hand side is only read
+    dwp::launch_vacuum_solve(c->stream, c->plan, c->fx, c->fy, c->fz, const_cast<double *>(r), nullptr, c->cbuf.p, out,
                              nullptr, c->opts.fft_fp32 != 0);
     ABI_END(c)
 }
@@ -1590,7 +1605,7 @@ int dwp_apply_split(dwp_ctx *c, const double *r, double *out) {
     dwp::need_eps(c);
     if (!r || !out) dwp::fail(DWP_EINVAL, "NULL pointer");
     DWP_HIP(hipSetDevice(c->device));
-    dwp::apply_split(c, r, out);
+    dwp::apply_split(c, const_cast<double *>(r), out);  // without a rescaling r is only read
     ABI_END(c)
 }
 

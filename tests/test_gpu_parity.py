@@ -160,6 +160,24 @@ def test_solve_small_slab_float32_dry_update(torch, exclusion):
     _check_solution(torch, s, rho, eps, _host(phi), E, info, 1e-10, 1e-8)
 
 
+# restart cycles whose new vectors the dry update rescales as it reads them: planes in
+# one block and separate x passes (fewer than 64 planes of 96 x 96), with fewer blocks
+# of reductions than usual and with all of them
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n", [(16, 32, 24), (96, 96, 32)])
+def test_solve_with_rescaled_vectors(torch, n, precision):
+    L = (0.25 * n[0], 0.25 * n[1], 0.4 * n[2])
+    eps, rho = W.random_fields(n, 43)
+    rho -= rho.mean()
+    s = _solver(torch, n, L, z_wet_lo=0.3 * L[2], z_wet_hi=L[2], tol=1e-10, precision=precision, fft_fp32=precision,
+                krylov_fp32=precision, restart=8)
+    s.set_epsilon(_dev(torch, eps))
+    phi, E, info = s.solve(_dev(torch, rho))
+    assert info["restarts"] >= 2
+    # the bars of the other solves at this tolerance
+    _check_solution(torch, s, rho, eps, _host(phi), E, info, 1e-9, 1e-7)
+
+
 @pytest.mark.parametrize("exclusion", [False, True])
 def test_forces_and_eps_gradient_match_oracle(torch, exclusion):
     w = W.slab(n=(48, 48, 96), exclusion=exclusion)
