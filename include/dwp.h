@@ -228,6 +228,14 @@ int dwp_destroy(dwp_ctx *ctx);
 /* Change the stream later calls enqueue on. */
 int dwp_set_stream(dwp_ctx *ctx, void *hip_stream);
 
+/* Longest wait, in ms (0 .. 10000, default 100), of the workgroups that share
+ * the sweeps of a large coarsest level for one another: other work on the
+ * device can keep some of them from starting.  Sweeps whose wait was given up
+ * are repeated by one workgroup on its own, so the results do not depend on
+ * it; after eight of them the context takes one launch per sweep until the
+ * next dwp_set_grid.  0: no wait at all (every such launch is repeated). */
+int dwp_set_coarse_wait(dwp_ctx *ctx, double ms);
+
 /* Fix the grid and plan the solver (Sec. II.F: FFT plan for the whole cell,
  * multigrid hierarchy for the wet slab).  Each n_d must be even, at least 8,
  * with no prime factor other than 2 and 3 and at most 4096; L_d > 0; W must

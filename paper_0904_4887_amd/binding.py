@@ -62,6 +62,7 @@ _SIGNATURES = {
     "dwp_create": (C.c_int, [C.POINTER(_P), C.c_int, _P]),
     "dwp_destroy": (C.c_int, [_P]),
     "dwp_set_stream": (C.c_int, [_P, _P]),
+    "dwp_set_coarse_wait": (C.c_int, [_P, C.c_double]),
     "dwp_set_grid": (C.c_int, [_P, C.c_int, C.c_int, C.c_int, C.c_double, C.c_double, C.c_double,
                                C.POINTER(Opts)]),
     "dwp_set_opts": (C.c_int, [_P, C.POINTER(Opts)]),
@@ -196,6 +197,10 @@ class Solver:
 
     def empty(self):
         return self._torch.empty(self.shape, dtype=self._torch.float64, device=self.device)
+
+    def set_coarse_wait(self, ms):
+        """Longest wait (ms) of a large coarsest level's shared sweeps."""
+        self._check(lib().dwp_set_coarse_wait(self._h, float(ms)))
 
     def set_grid(self, n, L, **opts):
         self.epoch += 1

@@ -53,6 +53,18 @@ struct CoopPlan {
     int ty = 0, tz = 0, bym = 0, bzm = 0, K = 0, H = 0, nt = 0;
     size_t bytes = 0;
 };
+// What a context keeps for them: the face words, with the flag of a given-up
+// wait behind them, the last step number used in the words, the longest wait,
+// and (in pinned host memory, written by the device) how many launches gave up.
+// From COOP_GIVE_UPS on the context takes one launch per sweep.
+struct CoopState {
+    DevBuf halo;
+    unsigned tag = 0;
+    double wait_ms = 100.0;
+    int clock_khz = 0;            // of the device's wall clock
+    unsigned *gave_up = nullptr;
+};
+constexpr unsigned COOP_GIVE_UPS = 8;
 
 // One level of the wet-slab hierarchy.  Arrays of the unknowns and of eps hold
 // nw + 2 planes: plane 0 and plane nw + 1 are the Dirichlet planes next to the
@@ -201,8 +213,7 @@ struct dwp_ctx {
     double background = 0.0;      // uniform background of the last order-6 solve
     double first_cycle_red = -1.0;  // residual reduction of the last solve's first cycle (< 0: none yet)
     dwp::PhaseTimer phases;       // phase timers of the solve in progress
-    dwp::DevBuf coop_halo;        // face words of the coarsest level's cooperative sweeps
-    unsigned coop_tag = 0;        // and the last step number used in them
+    dwp::CoopState coop;          // cooperative sweeps of the coarsest level
     dwp::DevBuf bw_rhs, bw_lam;   // adjoint right-hand side and solution of dwp_backward
 };
 
@@ -300,11 +311,11 @@ template <class T>
 void launch_vcycle_bottom(hipStream_t s, const std::vector<Level *> &levels, size_t l0, int pre, int post,
                           int coarse_sweeps);
 // `sweeps` sweeps (colour 0 first) of a level's u in one cooperative launch on
-// many workgroups, which exchange their tiles' faces through `halo` (words
-// numbered from `tag` on); false, with nothing launched, where no tiling fits
-// or the stream is being captured
+// many workgroups, which exchange their tiles' faces; false, with nothing
+// launched, where no tiling fits, the stream is being captured or earlier
+// launches of the context have waited in vain too often
 template <class T>
-bool launch_coarse_coop(hipStream_t s, const Level &L, int sweeps, bool zero_in, DevBuf &halo, unsigned &tag);
+bool launch_coarse_coop(hipStream_t s, Level &L, int sweeps, bool zero_in, CoopState &st);
 constexpr int COOP_MIN_SWEEPS = 8;
 constexpr size_t BOTTOM_MAX_POINTS = 8192;     // levels this small (and below) go to the bottom kernel
 // points whose sweeps the bottom kernel keeps in registers (1024 threads, two

@@ -1442,13 +1442,16 @@ __global__ void __launch_bounds__(1024) k_vcycle_bottom_lds(Bottom<T> B, BottomL
 // step number is right holds the right value, so there is no flag to order
 // against and no fence.  Two copies of the words alternate: a workgroup can
 // write step s + 2 only after its neighbours have sent step s + 1, which they
-// do after they have read step s.  All workgroups are resident (cooperative
-// launch, at most one per CU), so every wait ends; a wait that still exceeds
-// COOP_SPINS polls gives up and puts NaN into u, which the Krylov solver
-// reports as a non-finite basis.  Measured in the solve (float64, 64 sweeps,
-// kernel trace): 54 x 48 x 127 points 217 us against 64 launches of 10.0 us,
-// 18 x 18 x 111 points 135 us against 64 of 7.1 us; what bounds it is the
-// exchange, 0.9 us a colour with few words.  Words are laid out so that a
+// do after they have read step s.  The cooperative launch sees to it that all
+// workgroups fit the device together (at most one per CU), not that they start
+// together: kernels of other streams or processes, or a stream bound to a part
+// of the CUs, can keep some of them out.  So a wait is bounded by the clock
+// (A.limit); a workgroup that gives up says so in *A.lost and goes on without
+// waiting, the launch's input stays as it was (the result goes to A.out), and
+// k_coarse_redo, launched behind it, then repeats the sweeps.  Measured in the
+// solve (float64, 64 sweeps, kernel trace): 54 x 48 x 127 points 217 us against
+// 64 launches of 10.0 us, 18 x 18 x 111 points 135 us against 64 of 7.1 us; what
+// bounds it is the exchange, 0.9 us a colour with few words.  Words are laid out so that a
 // wavefront's loads and stores are contiguous (the two words of a float64
 // apart: side by side they took 1.5 times as long).  Same operations on the
 // same values as the colour passes.
@@ -1456,15 +1459,18 @@ __global__ void __launch_bounds__(1024) k_vcycle_bottom_lds(Bottom<T> B, BottomL
 // and polls that come too early only load the fabric (54 x 48 x 127 points: 0 units
 // 1.15 times the whole gradient's time at 16; 12: 1.05; 24: 1.02)
 constexpr int COOP_WAIT = 16;
-constexpr int COOP_SPINS = 1 << 20;
+constexpr int COOP_CLOCK = 32;        // polls between two looks at the clock
 template <class T> struct CoopArgs {
-    T *u;                             // ghosted
+    const T *u;                       // ghosted
+    T *out;                           // ghosted, its ghost planes zero
     const T *e, *f;
     LevelArgs a;
     int sweeps, zero_in;
     int ty, tz, bym, bzm;             // tile counts, largest tile extents
     unsigned long long *halo;         // [2][tiles][face words]
     unsigned tag;                     // step numbers of this launch: tag + 1 ..
+    unsigned *lost;                   // set when a wait was given up
+    long long limit;                  // longest wait, in ticks of wall_clock64(); 0: none is waited for
 };
 
 template <class T> struct CoopWord;
@@ -1582,7 +1588,7 @@ __global__ void __launch_bounds__(NT) k_coarse_coop(CoopArgs<T> A) {
         rl[h] = ((rp * nr + rr) * nx + 2 * t) | ((rj + rk + 2) & 1);
         rw[h] = on[h] ? nt * stride * NWD + opp + x : 0;
     }
-    bool lost = false;
+    bool lost = A.limit == 0;
     __syncthreads();
     const int steps = 2 * A.sweeps;
     for (int st = 0; st < steps; st += 2) {
@@ -1615,7 +1621,8 @@ __global__ void __launch_bounds__(NT) k_coarse_coop(CoopArgs<T> A) {
             if (!last) {
                 unsigned part[H][NWD];
                 bool all = lost;
-                __builtin_amdgcn_s_sleep(COOP_WAIT);
+                long long since = 0;
+                if (!lost) __builtin_amdgcn_s_sleep(COOP_WAIT);
                 for (int spin = 0; !all; ++spin) {
                     if (spin) __builtin_amdgcn_s_sleep(2);
                     all = true;
@@ -1634,11 +1641,15 @@ __global__ void __launch_bounds__(NT) k_coarse_coop(CoopArgs<T> A) {
                             all = all && (unsigned)(x[h][q] >> 32) == tag;
                             part[h][q] = (unsigned)x[h][q];
                         }
-                    if (spin >= COOP_SPINS && !all) { lost = true; break; }
+                    if (!all && spin % COOP_CLOCK == COOP_CLOCK - 1) {
+                        const long long now = wall_clock64();
+                        if (since == 0) since = now;
+                        else if (now - since > A.limit) lost = all = true;
+                    }
                 }
 #pragma unroll
                 for (int h = 0; h < H; ++h)
-                    if (on[h]) lu[rl[h] ^ c] = lost ? T(__builtin_nanf("")) : CoopWord<T>::join(part[h]);
+                    if (on[h]) lu[rl[h] ^ c] = lost ? T(0) : CoopWord<T>::join(part[h]);
             }
             __syncthreads();
         }
@@ -1651,9 +1662,26 @@ __global__ void __launch_bounds__(NT) k_coarse_coop(CoopArgs<T> A) {
             if (q < per) {
                 const int t = q % half, r = (q / half) % by, pl = q / (half * by);
                 const int j = j0 + r, k = k0 + pl, i = 2 * t + ((j + k + c) & 1);
-                A.u[(size_t)(k + 1) * plane + j * nx + i] = lu[g[c][m]];
+                A.out[(size_t)(k + 1) * plane + j * nx + i] = lu[g[c][m]];
             }
         }
+    if (lost) __hip_atomic_store(A.lost, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The same sweeps by one workgroup out of global memory where the launch
+// before it has given a wait up, else nothing (an empty launch, 3 us).
+// *gave_up, in host memory, counts those.
+template <class T>
+__global__ void __launch_bounds__(1024) k_coarse_redo(CoopArgs<T> A, LevelDesc<T> d, unsigned *gave_up) {
+    if (*A.lost == 0) return;
+    const int plane = A.a.nx * A.a.ny, n = plane * A.a.nw;
+    for (int q = threadIdx.x; q < n; q += blockDim.x) A.out[plane + q] = A.zero_in ? T(0) : A.u[plane + q];
+    __syncthreads();
+    for (int s = 0; s < A.sweeps; ++s) { bt_smooth(d, 0); bt_smooth(d, 1); }
+    if (threadIdx.x == 0) {
+        *A.lost = 0;
+        __hip_atomic_store(gave_up, *gave_up + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 inline int grid1d(size_t n, int threads = 256) {
@@ -2224,18 +2252,7 @@ void launch_vcycle_bottom(hipStream_t s, const std::vector<Level *> &levels, siz
     Bottom<T> B{};
     B.nl = (int)(levels.size() - l0);
     if (B.nl < 1 || B.nl > MAX_BOTTOM) fail(DWP_EINVAL, "internal: bad bottom level count");
-    for (int l = 0; l < B.nl; ++l) {
-        const Level &L = *levels[l0 + l];
-        B.L[l].u = L.u.as<T>();
-        B.L[l].f = L.f.as<T>();
-        B.L[l].r = L.r.as<T>();
-        B.L[l].e = L.eps.as<T>();
-        B.L[l].a = level_args(L);
-        B.L[l].zc = L.zc ? 1 : 0;
-        B.L[l].mh = bt_magic(L.nx / 2);
-        B.L[l].mx = bt_magic(L.nx);
-        B.L[l].my = bt_magic(L.ny);
-    }
+    for (int l = 0; l < B.nl; ++l) B.L[l] = level_desc<T>(*levels[l0 + l]);
     B.pre = pre;
     B.post = post;
     B.coarse = coarse_sweeps;
@@ -2303,6 +2320,19 @@ template <class T> static const CoopPlan &coop_plan(const Level &L) {
     }
     return best;
 }
+template <class T> static LevelDesc<T> level_desc(const Level &L) {
+    LevelDesc<T> d;
+    d.u = L.u.as<T>();
+    d.f = L.f.as<T>();
+    d.r = L.r.as<T>();
+    d.e = L.eps.as<T>();
+    d.a = level_args(L);
+    d.zc = L.zc ? 1 : 0;
+    d.mh = bt_magic(L.nx / 2);
+    d.mx = bt_magic(L.nx);
+    d.my = bt_magic(L.ny);
+    return d;
+}
 template <class T, int K, int H, int NT> static bool coop_launch(hipStream_t s, CoopArgs<T> &A, const CoopPlan &q) {
     const void *fn = reinterpret_cast<const void *>(&k_coarse_coop<T, K, H, NT>);
     if (occupancy(fn, NT, q.bytes) < 1) return false;
@@ -2311,7 +2341,8 @@ template <class T, int K, int H, int NT> static bool coop_launch(hipStream_t s, 
     return true;
 }
 template <class T>
-bool launch_coarse_coop(hipStream_t s, const Level &L, int sweeps, bool zero_in, DevBuf &halo, unsigned &tag) {
+bool launch_coarse_coop(hipStream_t s, Level &L, int sweeps, bool zero_in, CoopState &st) {
+    if (__atomic_load_n(st.gave_up, __ATOMIC_RELAXED) >= COOP_GIVE_UPS) return false;
     // a captured graph would replay the step numbers of its capture
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     DWP_HIP(hipStreamIsCapturing(s, &cap));
@@ -2319,23 +2350,30 @@ bool launch_coarse_coop(hipStream_t s, const Level &L, int sweeps, bool zero_in,
     const CoopPlan &q = coop_plan<T>(L);
     if (q.K == 0) return false;
     const int half = L.nx / 2;
+    // the face words, and the flag after them
     const size_t words = (size_t)2 * q.ty * q.tz * 2 * half * (q.bym + q.bzm) * CoopWord<T>::N;
     const unsigned steps = 2u * (unsigned)sweeps;
     // the words' step numbers only ever grow; a new buffer, or numbers about to
     // wrap, start from zeroed words
-    const bool fresh = halo.bytes < 8 * words || tag > 0x7FFFFFFFu - steps;
+    const bool fresh = st.halo.bytes < 8 * (words + 1) || st.tag > 0x7FFFFFFFu - steps;
     if (fresh) {
-        halo.alloc(8 * words);
-        launch_zero<double>(s, halo.as<double>(), halo.bytes / 8);
-        tag = 0;
+        st.halo.alloc(8 * (words + 1));
+        launch_zero<double>(s, st.halo.as<double>(), st.halo.bytes / 8);
+        st.tag = 0;
     }
-    CoopArgs<T> A{L.u.as<T>(), L.eps.as<T>(), L.f.as<T>(), level_args(L), sweeps, zero_in ? 1 : 0,
-                  q.ty, q.tz, q.bym, q.bzm, halo.as<unsigned long long>(), tag};
+    unsigned *lost = reinterpret_cast<unsigned *>(st.halo.as<char>() + st.halo.bytes - 8);
+    CoopArgs<T> A{L.u.as<T>(), L.u2.as<T>(), L.eps.as<T>(), L.f.as<T>(), level_args(L), sweeps, zero_in ? 1 : 0,
+                  q.ty, q.tz, q.bym, q.bzm, st.halo.as<unsigned long long>(), st.tag, lost,
+                  (long long)(st.wait_ms * st.clock_khz)};
     const bool ok = q.K == 3 ? coop_launch<T, 3, 2, 512>(s, A, q)
                     : q.K == 2 ? coop_launch<T, 2, 2, 512>(s, A, q)
                     : q.nt == 1024 ? coop_launch<T, 1, 1, 1024>(s, A, q) : coop_launch<T, 1, 1, 512>(s, A, q);
-    if (ok) tag += steps;
-    return ok;
+    if (!ok) return false;
+    st.tag += steps;
+    std::swap(L.u.p, L.u2.p);
+    k_coarse_redo<T><<<1, 1024, 0, s>>>(A, level_desc<T>(L), st.gave_up);
+    DWP_LAUNCH_CHECK();
+    return true;
 }
 
 template <class T>
@@ -2361,7 +2399,7 @@ void launch_zero(hipStream_t s, T *x, size_t n) {
     template void launch_prolong_add<T>(hipStream_t, const Level &, const Level &);                   \
     template void launch_coarsen_eps<T>(hipStream_t, const Level &, const Level &);                   \
     template void launch_zero<T>(hipStream_t, T *, size_t);                                          \
-    template bool launch_coarse_coop<T>(hipStream_t, const Level &, int, bool, DevBuf &, unsigned &); \
+    template bool launch_coarse_coop<T>(hipStream_t, Level &, int, bool, CoopState &);                \
     template void launch_vcycle_bottom<T>(hipStream_t, const std::vector<Level *> &, size_t, int, int, int);
 DWP_INST(float)
 DWP_INST(double)

@@ -367,7 +367,7 @@ bool vcycle(dwp_ctx *c, size_t l, bool u_unset, T *zadd) {
         npts > BOTTOM_REG_POINTS<T> && (sizeof(T) == 8 || !fused)) {
         const int ev = c->prof.begin(s, sg);
         const bool zero = l > 0 || u_unset;
-        const bool ok = launch_coarse_coop<T>(s, L, c->opts.coarse_sweeps, zero, c->coop_halo, c->coop_tag);
+        const bool ok = launch_coarse_coop<T>(s, L, c->opts.coarse_sweeps, zero, c->coop);
         if (ok) {
             c->prof.end(s, ev, sg, 2.0 * pass_bytes * c->opts.coarse_sweeps);
             return false;
@@ -916,6 +916,7 @@ void set_grid_impl(dwp_ctx *c, int nx, int ny, int nz, double Lx, double Ly, dou
     validate_opts(opts);
     c->have_grid = c->have_eps = c->have_solution = false;
     c->first_cycle_red = -1.0;
+    __atomic_store_n(c->coop.gave_up, 0u, __ATOMIC_RELAXED);
     free_levels(c);
     Plan &p = c->plan;
     p.nx = nx; p.ny = ny; p.nz = nz;
@@ -1422,7 +1423,12 @@ int dwp_create(dwp_ctx **out, int device, void *stream) {
         c->device = device;
         c->stream = static_cast<hipStream_t>(stream);
         c->host_len = 8192;
-        DWP_HIP(hipHostMalloc(reinterpret_cast<void **>(&c->host), sizeof(double) * c->host_len, hipHostMallocDefault));
+        // the staging values, and the device's count of given-up waits after them
+        DWP_HIP(hipHostMalloc(reinterpret_cast<void **>(&c->host), sizeof(double) * (c->host_len + 1),
+                              hipHostMallocDefault));
+        c->coop.gave_up = reinterpret_cast<unsigned *>(c->host + c->host_len);
+        *c->coop.gave_up = 0;
+        DWP_HIP(hipDeviceGetAttribute(&c->coop.clock_khz, hipDeviceAttributeWallClockRate, device));
         // the static scratch's address on this device, once per device
         if (device < dwp::MAX_DEVICES && !dwp::g_scratch_dev[device]) dwp::resolve_scratch(device);
         dwp_default_opts(&c->opts);
@@ -1449,6 +1455,13 @@ int dwp_destroy(dwp_ctx *c) {
 int dwp_set_stream(dwp_ctx *c, void *stream) {
     ABI_BEGIN(c)
     c->stream = static_cast<hipStream_t>(stream);
+    ABI_END(c)
+}
+
+int dwp_set_coarse_wait(dwp_ctx *c, double ms) {
+    ABI_BEGIN(c)
+    if (!(ms >= 0.0 && ms <= 10000.0)) dwp::fail(DWP_EINVAL, "the longest wait must lie in [0, 10000] ms");
+    c->coop.wait_ms = ms;
     ABI_END(c)
 }
 

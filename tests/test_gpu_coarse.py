@@ -1,0 +1,73 @@
+"""The cooperative sweeps of a large coarsest level when something goes wrong:
+waits that are given up, launches that the runtime refuses, device memory."""
+import numpy as np
+import pytest
+
+from paper_0904_4887_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    return torch
+
+
+def _solver(torch, n, precision=0, **opts):
+    from paper_0904_4887_amd.binding import Solver
+    L = (0.3 * n[0], 0.25 * n[1], 0.4 * n[2])
+    eps, r = W.random_fields(n, 31)
+    s = Solver(0)
+    s.set_grid(n, L, precision=precision, z_wet_lo=0.3 * L[2], z_wet_hi=L[2], **opts)
+    s.set_epsilon(torch.from_numpy(eps).cuda())
+    return s, torch.from_numpy(r).cuda()
+
+
+def _rel(a, b):
+    return float((a - b).abs().max() / b.abs().max())
+
+
+# one level alone (its second cycle goes on from the first one's values) and a
+# coarsest level under others; float32 takes these sweeps below 2^14 points
+@pytest.mark.parametrize("n,precision,opts", [
+    ((18, 18, 64), 0, dict(cycles=2)), ((18, 18, 64), 1, dict(cycles=2)), ((54, 54, 64), 0, dict(cycles=2)),
+    ((108, 96, 96), 0, dict()), ((36, 36, 96), 1, dict())])
+def test_sweeps_whose_wait_was_given_up_are_repeated(torch, n, precision, opts):
+    """With no wait at all every such launch gives up.  The results are those of
+    one launch per colour, whether the sweeps are repeated or, after eight
+    launches, no longer tried."""
+    s, r = _solver(torch, n, precision, **opts)
+    s.set_opts(smoother=0)
+    ref = s.apply_split(r)
+    s.set_opts(smoother=1)
+    ok = s.apply_split(r)
+    s.set_coarse_wait(0.0)
+    # the bars of the sweeps against colour passes
+    bar = 1e-12 if precision == 0 else 2e-5
+    assert _rel(ok, ref) <= bar
+    for _ in range(10):
+        z = s.apply_split(r)
+        assert _rel(z, ref) <= bar
+    s.close()
+
+
+def test_solve_with_waits_given_up(torch):
+    s, r = _solver(torch, (108, 96, 96), tol=1e-8)
+    r -= r.mean()
+    phi, E, info = s.solve(r)
+    s.set_coarse_wait(0.0)
+    phi0, E0, info0 = s.solve(r)
+    assert info0["rel_res"] <= 1e-8 and info0["outer_iters"] == info["outer_iters"]
+    assert abs(E0 - E) <= 1e-9 * abs(E)
+    s.close()
+
+
+@pytest.mark.parametrize("ms", [-1.0, 10001.0, float("nan")])
+def test_bad_coarse_wait_is_refused(torch, ms):
+    from paper_0904_4887_amd.binding import DWPError, DWP_EINVAL, Solver
+    s = Solver(0)
+    with pytest.raises(DWPError) as e:
+        s.set_coarse_wait(ms)
+    assert e.value.status == DWP_EINVAL
+    s.close()
