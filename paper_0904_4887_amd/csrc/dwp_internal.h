@@ -312,8 +312,9 @@ void launch_vcycle_bottom(hipStream_t s, const std::vector<Level *> &levels, siz
                           int coarse_sweeps);
 // `sweeps` sweeps (colour 0 first) of a level's u in one cooperative launch on
 // many workgroups, which exchange their tiles' faces; false, with nothing
-// launched, where no tiling fits, the stream is being captured or earlier
-// launches of the context have waited in vain too often
+// launched, where no tiling fits, the stream is being captured, the runtime
+// refuses the launch or earlier launches of the context have waited in vain too
+// often
 template <class T>
 bool launch_coarse_coop(hipStream_t s, Level &L, int sweeps, bool zero_in, CoopState &st);
 constexpr int COOP_MIN_SWEEPS = 8;

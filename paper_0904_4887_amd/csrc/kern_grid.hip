@@ -2337,15 +2337,20 @@ template <class T, int K, int H, int NT> static bool coop_launch(hipStream_t s, 
     const void *fn = reinterpret_cast<const void *>(&k_coarse_coop<T, K, H, NT>);
     if (occupancy(fn, NT, q.bytes) < 1) return false;
     void *args[] = {&A};
-    DWP_HIP(hipLaunchCooperativeKernel(fn, dim3(q.ty * q.tz), dim3(NT), args, (unsigned)q.bytes, s));
-    return true;
+    if (hipLaunchCooperativeKernel(fn, dim3(q.ty * q.tz), dim3(NT), args, (unsigned)q.bytes, s) == hipSuccess) return true;
+    (void)hipGetLastError();  // refused: the caller launches the sweeps one by one
+    return false;
 }
 template <class T>
 bool launch_coarse_coop(hipStream_t s, Level &L, int sweeps, bool zero_in, CoopState &st) {
     if (__atomic_load_n(st.gave_up, __ATOMIC_RELAXED) >= COOP_GIVE_UPS) return false;
-    // a captured graph would replay the step numbers of its capture
+    // a captured graph would replay the step numbers of its capture (the query
+    // itself fails on the null stream while another stream is captured)
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    DWP_HIP(hipStreamIsCapturing(s, &cap));
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
     if (cap != hipStreamCaptureStatusNone) return false;
     const CoopPlan &q = coop_plan<T>(L);
     if (q.K == 0) return false;

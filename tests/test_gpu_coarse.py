@@ -1,11 +1,16 @@
 """The cooperative sweeps of a large coarsest level when something goes wrong:
 waits that are given up, launches that the runtime refuses, device memory."""
-import numpy as np
+import os
+import subprocess
+import sys
+
 import pytest
 
 from paper_0904_4887_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.fixture(scope="module")
@@ -61,6 +66,44 @@ def test_solve_with_waits_given_up(torch):
     assert info0["rel_res"] <= 1e-8 and info0["outer_iters"] == info["outer_iters"]
     assert abs(E0 - E) <= 1e-9 * abs(E)
     s.close()
+
+
+_REFUSED = """
+import ctypes, sys
+# loaded before the HIP runtime, so that the library binds to this function
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+import torch
+from paper_0904_4887_amd import workloads as W
+from paper_0904_4887_amd.binding import Solver
+n = tuple(int(x) for x in sys.argv[2:5])
+L = (0.3 * n[0], 0.25 * n[1], 0.4 * n[2])
+eps, r = W.random_fields(n, 31)
+r = torch.from_numpy(r).cuda()
+s = Solver(0)
+s.set_grid(n, L, z_wet_lo=0.3 * L[2], z_wet_hi=L[2], smoother=0)
+s.set_epsilon(torch.from_numpy(eps).cuda())
+ref = s.apply_split(r)
+s.set_opts(smoother=1)
+z = s.apply_split(r)
+assert shim.refused() == 1
+d = float((z - ref).abs().max() / ref.abs().max())
+assert d <= 1e-12, d
+print("ok")
+"""
+
+
+@pytest.mark.parametrize("n", [(18, 18, 64), (108, 96, 96)])
+def test_refused_cooperative_launch_falls_back(torch, n, tmp_path):
+    """A runtime that refuses the cooperative launch (here a stand-in for its
+    entry, in a process of its own) leaves one launch per sweep."""
+    src, so = tmp_path / "refuse.c", tmp_path / "refuse.so"
+    src.write_text("static int n;\n"
+                   "int hipLaunchCooperativeKernel(void) { ++n; return 720; }  /* cooperative launch too large */\n"
+                   "int refused(void) { return n; }\n")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(so), str(src)], check=True)
+    p = subprocess.run([sys.executable, "-c", _REFUSED, str(so), *map(str, n)], cwd=ROOT, capture_output=True, text=True,
+                       timeout=100)
+    assert p.returncode == 0 and p.stdout.endswith("ok\n"), p.stdout + p.stderr
 
 
 @pytest.mark.parametrize("ms", [-1.0, 10001.0, float("nan")])
