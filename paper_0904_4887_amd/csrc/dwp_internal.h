@@ -317,6 +317,9 @@ void launch_vcycle_bottom(hipStream_t s, const std::vector<Level *> &levels, siz
 // often
 template <class T>
 bool launch_coarse_coop(hipStream_t s, Level &L, int sweeps, bool zero_in, CoopState &st);
+// and its face words, if some tiling of the level fits
+template <class T>
+void alloc_coarse_coop(hipStream_t s, const Level &L, CoopState &st);
 constexpr int COOP_MIN_SWEEPS = 8;
 constexpr size_t BOTTOM_MAX_POINTS = 8192;     // levels this small (and below) go to the bottom kernel
 // points whose sweeps the bottom kernel keeps in registers (1024 threads, two

@@ -2341,6 +2341,21 @@ template <class T, int K, int H, int NT> static bool coop_launch(hipStream_t s, 
     (void)hipGetLastError();  // refused: the caller launches the sweeps one by one
     return false;
 }
+// Bytes of the face words, with the flag after them.
+template <class T> static size_t coop_bytes(const Level &L, const CoopPlan &q) {
+    return 8 * ((size_t)2 * q.ty * q.tz * 2 * (L.nx / 2) * (q.bym + q.bzm) * CoopWord<T>::N + 1);
+}
+static void coop_clear(hipStream_t s, CoopState &st) {
+    launch_zero<double>(s, st.halo.as<double>(), st.halo.bytes / 8);
+    st.tag = 0;
+}
+template <class T> void alloc_coarse_coop(hipStream_t s, const Level &L, CoopState &st) {
+    if (L.n_interior() <= BOTTOM_REG_POINTS<T>) return;
+    const CoopPlan &q = coop_plan<T>(L);
+    if (q.K == 0) return;
+    st.halo.alloc(coop_bytes<T>(L, q));
+    coop_clear(s, st);
+}
 template <class T>
 bool launch_coarse_coop(hipStream_t s, Level &L, int sweeps, bool zero_in, CoopState &st) {
     if (__atomic_load_n(st.gave_up, __ATOMIC_RELAXED) >= COOP_GIVE_UPS) return false;
@@ -2353,19 +2368,11 @@ bool launch_coarse_coop(hipStream_t s, Level &L, int sweeps, bool zero_in, CoopS
     }
     if (cap != hipStreamCaptureStatusNone) return false;
     const CoopPlan &q = coop_plan<T>(L);
-    if (q.K == 0) return false;
-    const int half = L.nx / 2;
-    // the face words, and the flag after them
-    const size_t words = (size_t)2 * q.ty * q.tz * 2 * half * (q.bym + q.bzm) * CoopWord<T>::N;
+    if (q.K == 0 || st.halo.bytes < coop_bytes<T>(L, q)) return false;
     const unsigned steps = 2u * (unsigned)sweeps;
-    // the words' step numbers only ever grow; a new buffer, or numbers about to
-    // wrap, start from zeroed words
-    const bool fresh = st.halo.bytes < 8 * (words + 1) || st.tag > 0x7FFFFFFFu - steps;
-    if (fresh) {
-        st.halo.alloc(8 * (words + 1));
-        launch_zero<double>(s, st.halo.as<double>(), st.halo.bytes / 8);
-        st.tag = 0;
-    }
+    // the words' step numbers only ever grow; numbers about to wrap start from
+    // zeroed words
+    if (st.tag > 0x7FFFFFFFu - steps) coop_clear(s, st);
     unsigned *lost = reinterpret_cast<unsigned *>(st.halo.as<char>() + st.halo.bytes - 8);
     CoopArgs<T> A{L.u.as<T>(), L.u2.as<T>(), L.eps.as<T>(), L.f.as<T>(), level_args(L), sweeps, zero_in ? 1 : 0,
                   q.ty, q.tz, q.bym, q.bzm, st.halo.as<unsigned long long>(), st.tag, lost,
@@ -2404,6 +2411,7 @@ void launch_zero(hipStream_t s, T *x, size_t n) {
     template void launch_prolong_add<T>(hipStream_t, const Level &, const Level &);                   \
     template void launch_coarsen_eps<T>(hipStream_t, const Level &, const Level &);                   \
     template void launch_zero<T>(hipStream_t, T *, size_t);                                          \
+    template void alloc_coarse_coop<T>(hipStream_t, const Level &, CoopState &);                      \
     template bool launch_coarse_coop<T>(hipStream_t, Level &, int, bool, CoopState &);                \
     template void launch_vcycle_bottom<T>(hipStream_t, const std::vector<Level *> &, size_t, int, int, int);
 DWP_INST(float)

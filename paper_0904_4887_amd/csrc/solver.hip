@@ -268,6 +268,7 @@ void alloc_levels(dwp_ctx *c) {
         L->r.alloc(tsize<T>() * L->n_interior());
         launch_zero<T>(c->stream, L->u.as<T>(), L->n_ghosted());
     }
+    alloc_coarse_coop<T>(c->stream, *c->plan.levels.back(), c->coop);
 }
 
 void ensure_levels(dwp_ctx *c) {

@@ -106,6 +106,27 @@ def test_refused_cooperative_launch_falls_back(torch, n, tmp_path):
     assert p.returncode == 0 and p.stdout.endswith("ok\n"), p.stdout + p.stderr
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+def test_no_device_memory_is_allocated_after_set_grid(torch, precision):
+    """What a split needs is there once the grid and eps are set, also when the
+    options change its precision or levels.  A first context runs the same calls,
+    for what the runtime itself sets up with the first launch of a kernel."""
+    n = (54, 54, 64) if precision == 0 else (36, 36, 96)
+    free = []
+    for _ in range(2):
+        s, r = _solver(torch, n, 1 - precision, max_levels=2, cycles=2)
+        out = torch.empty_like(r)
+        for kw in (dict(precision=precision), dict(max_levels=1), dict(precision=1 - precision, max_levels=2)):
+            s.set_opts(**kw)
+            torch.cuda.synchronize()
+            before = torch.cuda.mem_get_info()[0]
+            s.apply_split(r, out)
+            torch.cuda.synchronize()
+            free.append(before - torch.cuda.mem_get_info()[0])
+        s.close()
+    assert free[3:] == [0, 0, 0]
+
+
 @pytest.mark.parametrize("ms", [-1.0, 10001.0, float("nan")])
 def test_bad_coarse_wait_is_refused(torch, ms):
     from paper_0904_4887_amd.binding import DWPError, DWP_EINVAL, Solver
