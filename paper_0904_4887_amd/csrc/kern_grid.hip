@@ -2249,6 +2249,19 @@ bool launch_sweep_fused<double>(hipStream_t s, const Level &L, const double *uin
     return false;
 }
 
+template <class T> static LevelDesc<T> level_desc(const Level &L) {
+    LevelDesc<T> d;
+    d.u = L.u.as<T>();
+    d.f = L.f.as<T>();
+    d.r = L.r.as<T>();
+    d.e = L.eps.as<T>();
+    d.a = level_args(L);
+    d.zc = L.zc ? 1 : 0;
+    d.mh = bt_magic(L.nx / 2);
+    d.mx = bt_magic(L.nx);
+    d.my = bt_magic(L.ny);
+    return d;
+}
 template <class T, int TOP>
 static void bottom_lds(hipStream_t s, const Bottom<T> &B, const BottomLds &O, size_t bytes) {
     // the dynamic-LDS limit is raised once per device (the contexts of one
@@ -2339,19 +2352,6 @@ template <class T> static const CoopPlan &coop_plan(const Level &L) {
         if (best.K) break;
     }
     return best;
-}
-template <class T> static LevelDesc<T> level_desc(const Level &L) {
-    LevelDesc<T> d;
-    d.u = L.u.as<T>();
-    d.f = L.f.as<T>();
-    d.r = L.r.as<T>();
-    d.e = L.eps.as<T>();
-    d.a = level_args(L);
-    d.zc = L.zc ? 1 : 0;
-    d.mh = bt_magic(L.nx / 2);
-    d.mx = bt_magic(L.nx);
-    d.my = bt_magic(L.ny);
-    return d;
 }
 template <class T, int K, int H, int NT> static bool coop_launch(hipStream_t s, CoopArgs<T> &A, const CoopPlan &q) {
     const void *fn = reinterpret_cast<const void *>(&k_coarse_coop<T, K, H, NT>);
