@@ -107,6 +107,7 @@ __host__ __device__ __forceinline__ T band_point(T cx, T cy, T cz, T e0, T exp, 
 template <class T, int W, bool ZIN, bool DOWN, int PD, bool PRO = false>
 struct BandSweep {
     typedef typename BandVec<T, W>::V V;
+    typedef V VZ __attribute__((aligned(8)));  // z may be a caller's float64 array, aligned to 8 bytes
     static constexpr int H = W / 2;         // points of each colour in a vector
     static constexpr int D = DOWN ? -1 : 1;  // direction of the march
 
@@ -436,7 +437,7 @@ struct BandSweep {
             if (a.zadd && valid) {
                 T *zd = a.zadd + (size_t)((a.kw0 + k) % a.nzb) * plane + ou;
                 BAND_CHECK((size_t)(zd - a.zadd) + W - 1, (size_t)a.nzb * plane);
-                *(V *)zd = *(const V *)zd + o;
+                *(VZ *)zd = *(const VZ *)zd + o;
             } else {
                 T *dst = a.uout + (valid ? (size_t)(k + 1) * plane : 0) + ou;
                 BAND_CHECK((size_t)(dst - a.uout) + W - 1, (size_t)(a.nw + 2) * plane);

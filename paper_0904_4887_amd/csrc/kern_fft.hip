@@ -307,6 +307,15 @@ template <class V> __device__ __forceinline__ void rescale(V &v, double f, int n
     for (int q = 0; q < n; ++q) v[q] = (decltype(v[q] + v[q]))((double)v[q] * f);
 }
 
+// W values of a row, and the same as they lie in memory: the rows of float64
+// arrays may be a caller's, which are aligned to 8 bytes only (gfx950 loads 16
+// bytes from any 4-byte boundary, so the code is that of aligned vectors).
+template <class T, int W> struct RowVec {
+    typedef T V __attribute__((ext_vector_type(W)));
+    typedef T M __attribute__((ext_vector_type(W), aligned(sizeof(T) == 8 ? 8 : W * sizeof(T))));
+};
+static_assert(alignof(RowVec<double, 2>::M) == 8 && alignof(RowVec<double, 4>::M) == 8);
+
 // ---------------------------------------------------------------- x passes
 // Rows are the nx-long x lines of the [nz][ny][nx] grid; B = 2^lb complex
 // lines per block carry 2B real rows.  LDS lines are padded to n + 1 elements.
@@ -320,7 +329,8 @@ k_fft_x_fwd(TI *in, const double *__restrict__ sinv, cplx<S> *__restrict__ out,
             Radices rd, const cplx<S> *__restrict__ tw, int lb, int nrows, int nkx, int ldc, Div dw, Div dk,
             Div dk2, Rescale rs) {
     using C = cplx<S>;
-    typedef std::remove_const_t<TI> TIW __attribute__((ext_vector_type(W)));
+    typedef RowVec<std::remove_const_t<TI>, W> RI;
+    typedef typename RI::V TIW;
     typedef double DW __attribute__((ext_vector_type(W)));
     extern __shared__ __align__(16) unsigned char lds_raw[];
     C *lds = reinterpret_cast<C *>(lds_raw);
@@ -345,8 +355,8 @@ k_fft_x_fwd(TI *in, const double *__restrict__ sinv, cplx<S> *__restrict__ out,
                     const int ra = r0 + 2 * l;
                     if (ra + 1 < nrows) {
                         const size_t ia = (size_t)ra * n + W * t;
-                        va[m] = *reinterpret_cast<const TIW *>(in + ia);
-                        vb[m] = *reinterpret_cast<const TIW *>(in + ia + n);
+                        va[m] = *reinterpret_cast<const typename RI::M *>(in + ia);
+                        vb[m] = *reinterpret_cast<const typename RI::M *>(in + ia + n);
                         if constexpr (SC) {
                             sa[m] = *reinterpret_cast<const DW *>(sinv + ia);
                             sb[m] = *reinterpret_cast<const DW *>(sinv + ia + n);
@@ -370,8 +380,8 @@ k_fft_x_fwd(TI *in, const double *__restrict__ sinv, cplx<S> *__restrict__ out,
                             TI *x = in + (size_t)ra * n + W * t;
                             rescale(va[m], fac, W);
                             rescale(vb[m], fac, W);
-                            *reinterpret_cast<TIW *>(x) = va[m];
-                            *reinterpret_cast<TIW *>(x + n) = vb[m];
+                            *reinterpret_cast<typename RI::M *>(x) = va[m];
+                            *reinterpret_cast<typename RI::M *>(x + n) = vb[m];
                         }
                     }
                 }
@@ -445,7 +455,7 @@ k_fft_x_inv(const cplx<S> *__restrict__ in, const double *__restrict__ sinv, TO 
     using C = cplx<S>;
     constexpr int KN = 16 / sizeof(C);
     typedef S SV __attribute__((ext_vector_type(2 * KN)));
-    typedef TO TOW __attribute__((ext_vector_type(W)));
+    typedef RowVec<TO, W> RO;
     typedef double DW __attribute__((ext_vector_type(W)));
     extern __shared__ __align__(16) unsigned char lds_raw[];
     C *lds = reinterpret_cast<C *>(lds_raw);
@@ -500,7 +510,7 @@ k_fft_x_inv(const cplx<S> *__restrict__ in, const double *__restrict__ sinv, TO 
             sa = *reinterpret_cast<const DW *>(sinv + ia);
             sb = *reinterpret_cast<const DW *>(sinv + ia + n);
         }
-        TOW a, b;
+        typename RO::V a, b;
 #pragma unroll
         for (int q = 0; q < W; ++q) {
             const C z = lds[l * ls + W * t + q];
@@ -512,8 +522,8 @@ k_fft_x_inv(const cplx<S> *__restrict__ in, const double *__restrict__ sinv, TO 
                 b[q] = (TO)z.y;
             }
         }
-        *reinterpret_cast<TOW *>(out + ia) = a;
-        *reinterpret_cast<TOW *>(out + ia + n) = b;
+        *reinterpret_cast<typename RO::M *>(out + ia) = a;
+        *reinterpret_cast<typename RO::M *>(out + ia + n) = b;
     }
 }
 
@@ -641,7 +651,8 @@ k_fft_xy_fwd(TI *in, const double *__restrict__ sinv, cplx<S> *__restrict__ out,
              Div dk, Rescale rs) {
     using C = cplx<S>;
     constexpr int MAXE = PE * NT;
-    typedef std::remove_const_t<TI> TIW __attribute__((ext_vector_type(2)));
+    typedef RowVec<std::remove_const_t<TI>, 2> RI;
+    typedef typename RI::V TIW;
     typedef double DW __attribute__((ext_vector_type(2)));
     extern __shared__ __align__(16) unsigned char lds_raw[];
     C *lds = reinterpret_cast<C *>(lds_raw);
@@ -660,8 +671,8 @@ k_fft_xy_fwd(TI *in, const double *__restrict__ sinv, cplx<S> *__restrict__ out,
             if (e < nl * nw) {
                 const int l = udiv(e, dw), t = e - l * nw;
                 const size_t ia = (z * ny + 2 * l) * n + 2 * t;
-                va[m] = *reinterpret_cast<const TIW *>(in + ia);
-                vb[m] = *reinterpret_cast<const TIW *>(in + ia + n);
+                va[m] = *reinterpret_cast<const typename RI::M *>(in + ia);
+                vb[m] = *reinterpret_cast<const typename RI::M *>(in + ia + n);
                 if constexpr (SC) {
                     sa[m] = *reinterpret_cast<const DW *>(sinv + ia);
                     sb[m] = *reinterpret_cast<const DW *>(sinv + ia + n);
@@ -680,8 +691,8 @@ k_fft_xy_fwd(TI *in, const double *__restrict__ sinv, cplx<S> *__restrict__ out,
                         TI *x = in + (z * ny + 2 * l) * n + 2 * t;
                         rescale(va[m], fac, 2);
                         rescale(vb[m], fac, 2);
-                        *reinterpret_cast<TIW *>(x) = va[m];
-                        *reinterpret_cast<TIW *>(x + n) = vb[m];
+                        *reinterpret_cast<typename RI::M *>(x) = va[m];
+                        *reinterpret_cast<typename RI::M *>(x + n) = vb[m];
                     }
                 }
             }
@@ -742,7 +753,7 @@ k_fft_xy_inv(const cplx<S> *__restrict__ in, const double *__restrict__ sinv, TO
              Div dk) {
     using C = cplx<S>;
     constexpr int MAXE = PE * NT;
-    typedef TO TOW __attribute__((ext_vector_type(2)));
+    typedef RowVec<TO, 2> RO;
     typedef double DW __attribute__((ext_vector_type(2)));
     extern __shared__ __align__(16) unsigned char lds_raw[];
     C *lds = reinterpret_cast<C *>(lds_raw);
@@ -792,7 +803,7 @@ k_fft_xy_inv(const cplx<S> *__restrict__ in, const double *__restrict__ sinv, TO
         const int l = udiv(e, dw), t = e - l * nw;
         const size_t ia = (z * ny + 2 * l) * n + 2 * t;
         const C v0 = lds[l * ls + 2 * t], v1 = lds[l * ls + 2 * t + 1];
-        TOW a, b;
+        typename RO::V a, b;
         if constexpr (SC) {
             const DW sa = *reinterpret_cast<const DW *>(sinv + ia), sb = *reinterpret_cast<const DW *>(sinv + ia + n);
             a[0] = (TO)((double)v0.x * sa[0]);
@@ -805,8 +816,8 @@ k_fft_xy_inv(const cplx<S> *__restrict__ in, const double *__restrict__ sinv, TO
             b[0] = (TO)v0.y;
             b[1] = (TO)v1.y;
         }
-        *reinterpret_cast<TOW *>(out + ia) = a;
-        *reinterpret_cast<TOW *>(out + ia + n) = b;
+        *reinterpret_cast<typename RO::M *>(out + ia) = a;
+        *reinterpret_cast<typename RO::M *>(out + ia + n) = b;
     }
 }
 
