@@ -327,6 +327,11 @@ void to_host(dwp_ctx *c, const double *dev, size_t n) {
     sync(c);
 }
 
+// Bytes per point of the sixth-order operator in float64: x and eps read (D1 eps
+// is formed from eps), out written; transposed, D1 eps is read too.  (The wet
+// residual reads v where the operator writes out, and its output counts apart.)
+double op6_bytes(const dwp_ctx *c) { return c->transposed ? 48.0 : 24.0; }
+
 // One V-cycle from level l down.  Coarse levels enter with a zero correction
 // (the restriction zeroes it); on the fine level, u_unset says that the
 // correction array holds stale values that must act as zero (first cycle),
@@ -475,7 +480,7 @@ void split_impl(dwp_ctx *c, TV *v, TZ *z, const Rescale &rs) {
         PROF(c, PG_WET, (8.0 + sizeof(TZ) + sizeof(T)) * nW,
              launch_wet_residual_v32<T>(s, p, v, z, c->eps32.as<float>(), F.f.as<T>()));
     } else if (c->opts.order == 6) {
-        PROF(c, PG_WET, (48.0 + sizeof(T)) * nW,
+        PROF(c, PG_WET, (op6_bytes(c) + sizeof(T)) * nW,
              launch_wet_residual6<T>(s, p, v, z, c->eps.as<double>(), c->G6.as<double>(), F.f.as<T>(),
                                      c->transposed));
     } else {
@@ -531,8 +536,7 @@ void apply_operator(dwp_ctx *c, const double *x, const double *b, double *out, b
         return;
     }
     double *coef = c->coef.as<double>();
-    // x, eps and the three components of D1 eps read, out written (+ b read)
-    PROF(c, PG_APPLY, (residual ? 56.0 : 48.0) * N,
+    PROF(c, PG_APPLY, op6_bytes(c) * N + (residual ? 8.0 : 0.0) * N,
          launch_apply6(s, p, x, c->eps.as<double>(), c->G6.as<double>(), b, out, residual, c->transposed));
     PROF(c, PG_VEC, 8.0 * N, launch_sum(s, out, N, c->partial.as<double>(), coef + 410));
     PROF(c, PG_VEC, 16.0 * N, launch_sub_mean(s, out, coef + 410, 1.0 / (double)N, N));
@@ -727,7 +731,7 @@ int fgmres(dwp_ctx *c, const double *b, double bnorm, double *x, int *restarts, 
                     // A6 z (A6^T z) without the separate removal of its mean: the
                     // projection also sums the new vector and the update takes
                     // the constant direction out with the others
-                    PROF(c, PG_APPLY, 48.0 * N,
+                    PROF(c, PG_APPLY, op6_bytes(c) * N,
                          launch_apply6(s, p, Zj, c->eps.as<double>(), c->G6.as<double>(), nullptr, Vn, false,
                                        c->transposed));
                     PROF(c, PG_MULTIDOT, md,

@@ -310,3 +310,26 @@ def test_exclusion_slab_converges_with_the_fft_dry_update(torch):
     r -= r.mean()
     assert float(r.norm() / b.norm()) <= 1.000001e-8
     s.close()
+
+
+def test_profile_counts_the_bytes_the_operator_moves(torch):
+    """24 bytes a point and application (x and eps read, out written), 32 for a
+    residual, 24 more with the transpose, which reads D1 eps."""
+    n, L = (24, 32, 36), (6.0, 8.0, 9.0)
+    x = np.cos(2.0 * math.pi * np.arange(n[0]) / n[0])
+    _, rho = W.random_fields(n, 41)
+    s = _solver(n, L, z_wet_lo=0.3 * L[2], z_wet_hi=L[2], cycles=0, tol=1e-8, profile=1)
+    s.set_epsilon(_dev(torch, np.broadcast_to(1.5 + 0.4 * x, rho.shape)))
+    rho = _dev(torch, rho - rho.mean())
+    s.profile_reset()
+    _, _, info = s.solve(rho)
+    ap = s.profile()["apply_full"]
+    N = n[0] * n[1] * n[2]
+    assert ap["launches"] == info["outer_iters"] + info["restarts"] + 1
+    assert ap["bytes"] == N * (24 * info["outer_iters"] + 32 * (info["restarts"] + 1))
+    s.profile_reset()
+    s.eps_gradient()
+    ap = s.profile()["apply_full"]
+    residuals, rest = divmod(ap["bytes"] - 48 * N * ap["launches"], 8 * N)
+    assert rest == 0 and 2 <= residuals < ap["launches"] / 2
+    s.close()
