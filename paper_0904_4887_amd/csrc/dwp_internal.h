@@ -225,6 +225,11 @@ constexpr int RED_THREADS = 256;
 // ----------------------------------------------------------------------------
 // Launchers (defined in the kernel translation units).
 
+// Resident blocks per CU of a kernel at a block shape (threads, dynamic LDS
+// bytes), and the CUs, of the current device.
+int occupancy(const void *fn, int nt, size_t bytes);
+int cu_count();
+
 // kern_grid.hip: full-box stencils
 void launch_apply_full(hipStream_t s, const Plan &p, const double *phi, const double *eps,
                        const double *b, double *out, bool residual);

@@ -8,6 +8,7 @@
 //             1/2 (eps_n + eps_m) (u_m - u_n) / h_d^2.
 #include <algorithm>
 #include <atomic>
+#include <map>
 #include <mutex>
 
 #include "dwp_internal.h"
@@ -1726,44 +1727,46 @@ LevelArgs level_args(const Level &L) {
 // ============================================================== launchers
 static bool al16(const void *q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; }
 
-// Resident blocks per CU of a kernel at a block shape (threads, dynamic LDS
-// bytes), cached per device: the occupancy query is a host call per launch
-// otherwise.  The raised dynamic-LDS limit is set the first time a kernel is
-// seen on a device.
-struct OccKey {
-    const void *fn;
-    int dev, nt;
-    size_t bytes;
-    int per;
-};
-static int occupancy(const void *fn, int nt, size_t bytes) {
-    static OccKey cache[64];
-    static int used = 0;
+// Cached per device: the occupancy query is a host call per launch otherwise.
+// The raised dynamic-LDS limit is set the first time a kernel is seen on a
+// device.  Bounded: past OCC_SHAPES shapes (some 100 grids') it starts again.
+constexpr size_t OCC_SHAPES = 2048;
+int occupancy(const void *fn, int nt, size_t bytes) {
+    static std::map<std::pair<const void *, int>, std::map<std::pair<int, size_t>, int>> cache;
+    static size_t used = 0;
     static std::mutex mu;
     std::lock_guard<std::mutex> lock(mu);
     int dev = 0;
     DWP_HIP(hipGetDevice(&dev));
-    bool seen = false;
-    for (int i = 0; i < used; ++i) {
-        const OccKey &k = cache[i];
-        if (k.fn == fn && k.dev == dev) {
-            seen = true;
-            if (k.nt == nt && k.bytes == bytes) return k.per;
-        }
+    if (used >= OCC_SHAPES) {
+        cache.clear();
+        used = 0;
     }
-    if (!seen) DWP_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)BOTTOM_LDS_BYTES));
-    int per = 0;
-    DWP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, nt, bytes));
-    if (used < 64) cache[used++] = OccKey{fn, dev, nt, bytes, per};
-    return per;
+    auto kernel = cache.find({fn, dev});
+    if (kernel == cache.end()) {
+        DWP_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)BOTTOM_LDS_BYTES));
+        kernel = cache.emplace(std::make_pair(fn, dev), std::map<std::pair<int, size_t>, int>()).first;
+    }
+    auto shape = kernel->second.find({nt, bytes});
+    if (shape == kernel->second.end()) {
+        int per = 0;
+        DWP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, nt, bytes));
+        shape = kernel->second.emplace(std::make_pair(nt, bytes), per).first;
+        ++used;
+    }
+    return shape->second;
 }
-static int cu_count() {
-    static int cus[64] = {0};
+int cu_count() {
+    static std::atomic<int> cus[64];
     int dev = 0;
     DWP_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= 64) fail(DWP_EINVAL, "internal: device index out of range");
-    if (!cus[dev]) DWP_HIP(hipDeviceGetAttribute(&cus[dev], hipDeviceAttributeMultiprocessorCount, dev));
-    return cus[dev];
+    int n = cus[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        DWP_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
+        cus[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
 }
 
 // The operator on row bands: false (nothing launched) where the shape does

@@ -13,7 +13,6 @@
 #include "dwp_internal.h"
 
 #include <algorithm>
-#include <mutex>
 
 namespace dwp {
 
@@ -563,30 +562,6 @@ void launch_d1eps(hipStream_t s, const Plan &p, const double *eps, double *G) {
     DWP_LAUNCH_CHECK();
 }
 
-// Resident blocks of a kernel on the whole device at a block shape, cached per
-// device (a query is a host call per launch otherwise).
-static int op6_slots(const void *fn, int nt, size_t bytes) {
-    struct Key { const void *fn; int dev, nt; size_t bytes; int slots; };
-    static std::vector<Key> cache;
-    static std::mutex mu;
-    std::lock_guard<std::mutex> lock(mu);
-    int dev = 0;
-    DWP_HIP(hipGetDevice(&dev));
-    bool seen = false;
-    for (const Key &k : cache) {
-        if (k.fn != fn || k.dev != dev) continue;
-        seen = true;
-        if (k.nt == nt && k.bytes == bytes) return k.slots;
-    }
-    if (!seen) DWP_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-    int cus = 0, per = 0;
-    DWP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    DWP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, nt, bytes));
-    const int slots = std::max(1, cus * per);
-    if (cache.size() < 256) cache.push_back(Key{fn, dev, nt, bytes, slots});
-    return slots;
-}
-
 // Tile and chunk of the operator: the widest tile row of whole pairs up to 48
 // that divides nx (48 pairs of 96 points, 32 of a power of two), as many rows
 // as divide ny within the kernel's threads (32 at most), and the chunk length
@@ -610,7 +585,7 @@ static Op6Shape op6_shape(const Plan &p, int k_w0, int nplanes, const void *fn, 
     const int nh = 4 * s.ty + 2 * H6Y * s.wp;  // halo pairs, one per thread
     nt = (std::max(s.wp * s.ty, nh) + 63) / 64 * 64;
     bytes = sizeof(double) * 2 * fields * (size_t)(s.ty + 2 * H6Y) * (2 * s.wp + 2 * H6X);
-    const long slots = (long)op6_slots(fn, nt, bytes);
+    const long slots = (long)std::max(1, cu_count() * occupancy(fn, nt, bytes));
     const long tiles = (long)s.tiles_x * s.tiles_y;
     long best = -1;
     for (int c = 1; c <= 64; ++c) {
