@@ -938,15 +938,16 @@ int tile_log2(int n, int budget) {
 // Larger ones need the planes to occupy the chip: a block's chain of stages
 // takes what it takes however few there are (96 x 96 in float64: 29 us by
 // separate passes and 31 in one at nz = 8, 39 and 37.5 at 64, 70 and 51 at
-// 192).  Past PLANE_MID one block fills a CU, so the last round over the 256
+// 192).  Past PLANE_MID one block fills a CU, so the last round over the (256)
 // CUs has to be worth it (128 x 128: 112 and 114 us at nz = 288, 138 and 127
 // at 384, 182 and 185 at 576; 40 and 48 at 32, 54 and 54 at 64).
 constexpr int PLANE_SMALL = 6 * 512, PLANE_MID = 6 * 1024, PLANE_MAX = 10 * 1024;
 bool plane_pass(int pv, size_t bytes, int nz) {
     if (pv <= PLANE_SMALL) return true;
     if (pv <= PLANE_MID) return nz >= 64;
-    const int last = nz % 256;
-    return pv <= PLANE_MAX && bytes <= 160 * 1024 && (last == 0 || last >= 96);
+    if (pv > PLANE_MAX || bytes > 160 * 1024) return false;
+    const int cus = cu_count(), last = nz % cus;
+    return last == 0 || 8 * last >= 3 * cus;
 }
 
 }  // namespace
