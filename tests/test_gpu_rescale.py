@@ -5,8 +5,9 @@ With the dry update alone and a permittivity close to constant A L^-1 v is close
 to v, the projection cancels most of it, and the norm that Pythagoras gives is
 off by much more than the rescaling's threshold (1e-8, or 1e-6 for a float32
 basis).  A host emulation of the cycle shows that it is, in steps whose
-rescaling is left to the next dry update, and what the cycle comes to when the
-stored vector is not rescaled, or rescaled twice."""
+rescaling is left to the next dry update, and what a cycle on a float32 basis
+comes to when the stored vector is not rescaled, or rescaled twice.  (On a
+float64 basis a norm just under the threshold costs as much as that.)"""
 import numpy as np
 import pytest
 
@@ -61,26 +62,58 @@ def _cycles(eps, b, h, f32, m, cycles, times=1):
 
 
 # planes in one block; separate passes with rows of 4 m and of 4 m + 2 values
-@pytest.mark.parametrize("n", [(16, 32, 24), (96, 96, 32), (162, 96, 16)])
-@pytest.mark.parametrize("f32,opts", [
-    (False, dict(precision=0)), (False, dict(precision=1, fft_fp32=1)),
-    (True, dict(precision=1, krylov_fp32=1)), (True, dict(precision=1, krylov_fp32=1, fft_fp32=1))])
-def test_deferred_rescaling(torch, n, f32, opts):
+SIZES = [(16, 32, 24), (96, 96, 32), (162, 96, 16)]
+
+
+def _solver(torch, n, spread, **opts):
     from paper_0904_4887_amd.binding import Solver
-    spread, m, cycles = (0.3, 6, 2) if f32 else (1e-3, 4, 1)
     L = (0.25 * n[0], 0.25 * n[1], 0.4 * n[2])
     eps, rho = W.random_fields(n, 43, 1.0, 1.0 + spread)
     rho -= rho.mean()
     s = Solver(0)
     # a tolerance out of reach: the host reads no step between the first and the last
-    s.set_grid(n, L, z_wet_lo=0.3 * L[2], z_wet_hi=L[2], cycles=0, tol=1e-300, restart=m, max_outer=m * cycles, **opts)
+    s.set_grid(n, L, z_wet_lo=0.3 * L[2], z_wet_hi=L[2], cycles=0, tol=1e-300, **opts)
     s.set_epsilon(torch.from_numpy(eps).cuda())
+    return s, eps, rho
+
+
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("opts", [dict(), dict(fft_fp32=1)])
+def test_deferred_rescaling_of_a_float32_basis(torch, n, opts):
+    m, cycles = 6, 2
+    s, eps, rho = _solver(torch, n, 0.3, precision=1, krylov_fp32=1, restart=m, max_outer=m * cycles, **opts)
     b = -4.0 * np.pi * rho
-    good, off = _cycles(eps, b, s.h, f32, m, cycles)
-    assert off > (1e-5 if f32 else 1e-7), off
-    bad = min(_cycles(eps, b, s.h, f32, m, cycles, t)[0] for t in (0, 2))
+    good, off = _cycles(eps, b, s.h, True, m, cycles)
+    assert off > 1e-5, off
+    bad = min(_cycles(eps, b, s.h, True, m, cycles, t)[0] for t in (0, 2))
     assert bad > 100 * good, (bad, good)
     phi, E, info = s.solve(torch.from_numpy(rho).cuda(), allow_noconv=True)
     assert info["outer_iters"] == m * cycles
     assert info["rel_res"] <= 10 * good, (info["rel_res"], good, bad)
+    s.close()
+
+
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("spread,opts", [
+    (1e-3, dict(precision=0)), (1e-3, dict(precision=1, fft_fp32=1)),
+    (0.3, dict(precision=1, krylov_fp32=1)), (0.3, dict(precision=1, krylov_fp32=1, fft_fp32=1))])
+def test_deferred_rescaling_equals_the_separate_kernel(torch, n, spread, opts):
+    """A cycle of four steps twice: with a tolerance out of reach, where the second
+    and third vector are left to the next dry update, and with one that the
+    first step's reduction predicts to be met before the fourth step, so that the
+    host reads every step and a kernel of its own rescales each vector.  The
+    results are the same bits."""
+    f32, m = spread == 0.3, 4
+    s, eps, rho = _solver(torch, n, spread, restart=m, max_outer=m, **opts)
+    good, off = _cycles(eps, -4.0 * np.pi * rho, s.h, f32, m, 1)
+    assert off > (1e-5 if f32 else 1e-7), off
+    rho = torch.from_numpy(rho).cuda()
+    phi, E, info = s.solve(rho, allow_noconv=True)
+    assert info["outer_iters"] == m
+    s.set_opts(max_outer=1)
+    first = s.solve(rho, allow_noconv=True)[2]["rel_res"]
+    s.set_opts(max_outer=m, tol=first**3.7)
+    phi1, E1, info1 = s.solve(rho, allow_noconv=True)
+    assert info1["outer_iters"] == m
+    assert torch.equal(phi, phi1) and E == E1
     s.close()
