@@ -1,9 +1,9 @@
 // Deterministic reductions and the Krylov vector kernels.
 //
-// Every reduction runs on a fixed grid of RED_BLOCKS blocks: each block
-// reduces its grid-stride share with wave64 shuffles and LDS and writes one
-// partial per output; a second kernel adds the partials of each output in a
-// fixed tree order.  Results are therefore bitwise reproducible.  The energy
+// Every reduction runs on a grid that its length fixes (RED_BLOCKS blocks at
+// most, none without an item): each block reduces its grid-stride share by wave
+// sums and LDS and writes one partial per output; a second kernel adds the
+// partials of each output in a fixed tree order.  Results are therefore bitwise reproducible.  The energy
 // sums use compensated (two-sum) accumulation throughout.
 #include "dwp_internal.h"
 
@@ -38,8 +38,8 @@ template <int O> __device__ __forceinline__ double lane_up(double v) {
 }
 // Sum over the wave, valid in lane 0: the tree of __shfl_down by 32, 16, .. 1,
 // bit for bit.  (Through the LDS, 12 permutes a sum and up to 33 sums a block:
-// 20.6 ms for the sixth-order step at 96 x 96 x 192, now 19.9; 60.8 and 60.5 for
-// the mixed slab step at 192 x 192 x 384.)
+// 20.6 ms for the sixth-order step at 96 x 96 x 192, now 19.9; on the mixed slab
+// step at 192 x 192 x 384 the difference is within the spread of the runs.)
 __device__ __forceinline__ double wave_sum(double v) {
     v += lane_up<32>(v);
     v += lane_up<16>(v);

@@ -2148,9 +2148,9 @@ static void sweep_fused_z(hipStream_t s, const Level &L, const T *uin, T *uout, 
 
 // Row-band sweep: returns false (and launches nothing) where the band shape
 // does not fit -- nx not a multiple of W, more than 1024 threads per block,
-// or no band height ty in BAND_ROWS that divides ny.  ty = 0 picks the first
-// height that fits; the chunk kc is chosen by the same round-filling cost
-// model as the tiled kernel's.
+// or no band height in BAND_ROWS that divides ny (the first that fits is
+// taken); the chunk kc is chosen by the same round-filling cost model as the
+// tiled kernel's.
 constexpr int BAND_ROWS[] = {12, 8, 16, 6, 4};
 template <class T, int W>
 static bool band_rows_fit(const Level &L, int t) {
