@@ -1427,8 +1427,8 @@ int dwp_create(dwp_ctx **out, int device, void *stream) {
         DWP_HIP(hipSetDevice(device));
         c->device = device;
         c->stream = static_cast<hipStream_t>(stream);
-        c->host_len = 8192;
-        // the staging values, and the device's count of given-up waits after them
+        // 64 KB: the staging values, and the device's count of given-up waits after them
+        c->host_len = 8191;
         DWP_HIP(hipHostMalloc(reinterpret_cast<void **>(&c->host), sizeof(double) * (c->host_len + 1),
                               hipHostMallocDefault));
         c->coop.gave_up = reinterpret_cast<unsigned *>(c->host + c->host_len);
