@@ -639,7 +639,7 @@ k_fft_y(cplx<S> *__restrict__ c, Radices rd, const cplx<S> *__restrict__ tw, int
 // form (PE per thread; what a stage keeps in registers).  Bound by the LDS
 // traffic and the barriers of a block's own chain of stages, the memory idle
 // meanwhile; the separate passes overlap their blocks but move the spectrum
-// four more times.  Whole solve, five passes against three, us: 27 -> 19.5 at
+// four more times.  Whole solve, five passes against three, us: 25.5 -> 18.4 at
 // 32 x 32 x 64, 70 -> 51 at 96 x 96 x 192, 106 -> 84 at 128 x 128 x 256 in
 // float64; 51.5 -> 40, 74 -> 55 in float32.  (Planes of up to 192 x 192 in
 // float32, 20 values a thread: 157 -> 187 us at 192 x 192 x 384, one block a

@@ -1470,7 +1470,7 @@ __global__ void __launch_bounds__(1024) k_vcycle_bottom_lds(Bottom<T> B, BottomL
 // (A.limit); a workgroup that gives up says so in *A.lost and goes on without
 // waiting, the launch's input stays as it was (the result goes to A.out), and
 // k_coarse_redo, launched behind it, then repeats the sweeps.  Measured in the
-// solve (float64, 64 sweeps, kernel trace): 54 x 48 x 127 points 217 us against
+// solve (float64, 64 sweeps, kernel trace): 54 x 48 x 127 points 221 us against
 // 64 launches of 10.0 us, 18 x 18 x 111 points 135 us against 64 of 7.1 us; what
 // bounds it is the exchange, 0.9 us a colour with few words.  Words are laid out so that a
 // wavefront's loads and stores are contiguous (the two words of a float64

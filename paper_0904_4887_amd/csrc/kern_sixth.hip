@@ -104,7 +104,7 @@ __global__ void __launch_bounds__(SX *SY) k_d1eps(Grid6 g, const double *__restr
 // Bound by HBM, LDS reads and float64 arithmetic alike at large grids (a plane
 // step spends about a microsecond of each per CU), by the latency of the steps
 // at small ones.  A6 at 192 x 192 x 384 in float64: 176 us with 64 x 4 tiles, two
-// barriers and unhidden loads a plane and G read; 86 us so.  On float32 vectors
+// barriers and unhidden loads a plane and G read; 91 us so.  On float32 vectors
 // at 96 x 96 x 192 (kernel trace): 30.4 -> 14.0 us, transposed 36.2 -> 23.2 us.
 constexpr int H6X = 4, H6Y = 3;             // halo columns (pair-aligned) and rows
 constexpr int OP6_NT_FWD = 768, OP6_NT_TRANS = 512;  // most threads (168 and 256 registers)
@@ -567,10 +567,11 @@ void launch_d1eps(hipStream_t s, const Plan &p, const double *eps, double *G) {
 // as divide ny within the kernel's threads (32 at most), and the chunk length
 // whose blocks fill whole rounds of the resident ones (a chunk costs its planes
 // and about five steps to fill its registers).  Tall tiles save halo work:
-// A6 at 192 x 192 x 384 takes 173 us with 4 rows of 48 pairs, 121 with 8, 86
-// with 16; 88 with 24 rows of 32 pairs, 91 with 32 rows of 24.  The transpose,
-// whose registers allow 512 threads, is fastest at 8 rows of 48 (768 threads
-// spill: 2 % more on the 128 x 128 x 256 step).
+// applied to the same arrays again and again, A6 at 192 x 192 x 384 takes 173 us
+// with 4 rows of 48 pairs, 121 with 8, 86 with 16; 88 with 24 rows of 32 pairs,
+// 91 with 32 rows of 24.  The transpose, whose registers allow 512 threads, is
+// fastest at 8 rows of 48 (768 threads spill: 2 % more on the 128 x 128 x 256
+// step).
 static Op6Shape op6_shape(const Plan &p, int k_w0, int nplanes, const void *fn, int most, int fields, int &nt,
                           size_t &bytes) {
     Op6Shape s{};
